@@ -17,6 +17,7 @@
 // merges the tiles of each row (m_R = max_t m, l_R = sum_t l 2^(m - m_R)),
 // normalises, and averages the B/S reduced rows of each query block.
 #include <atomic>
+#include <type_traits>
 
 #include "common.h"
 #include "score_rows.h"
@@ -70,7 +71,9 @@ __global__ __launch_bounds__(kThreads, 1) void score_partials(
   constexpr int S = kBlock / NRB;
   constexpr int KD = S * kHeadDim;  // reduced inner dimension S*d
   constexpr int NCH = KD / KC;      // >= 2 (S >= 1)
-  // [stage][operand A = K~ rows (c) | B = Q~ rows (R)][256 rows x 32]
+  // [operand A = K~ rows (c) | B = Q~ rows (R)][stage][256 rows x 64]: both
+  // stages of an operand lie within the 64 KB that an LDS read's constant
+  // offset reaches, so they share address registers
   __shared__ __attribute__((aligned(1024))) uint16_t lds[NSTAGE * 2 * kStage];
 
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
@@ -139,53 +142,88 @@ __global__ __launch_bounds__(kThreads, 1) void score_partials(
     const uint16_t* baseA = tKg + kap0;
     const uint16_t* baseB =
         tQh + __builtin_amdgcn_readlane(qsub_lane, kap0 / kHeadDim) * kHeadDim + kap0 % kHeadDim;
-    const uint32_t st = lds0 + (uint32_t)((ch % NSTAGE) * 2 * kStage * 2);
+    const uint32_t st = lds0 + (uint32_t)((ch % NSTAGE) * kStage * 2);
     const uint32_t row_lds = (uint32_t)((32 * wv + kDmaRows * i) * KC * 2);
     dma16(baseA, offA[i], st + row_lds);
-    dma16(baseB, offB[i], st + kStage * 2 + row_lds);
+    dma16(baseB, offB[i], st + NSTAGE * kStage * 2 + row_lds);
   };
 
   f32x16 acc[4][2];
 
+  // Operands of one 16-deep k-step: 4 K~ fragments (32 columns each), 2 Q~
+  // fragments (32 rows each). Two sets alternate: while the 8 MFMAs of a
+  // k-step run from one, the next k-step's 6 reads fill the other.
+  struct Frag {
+    u32x4 a[4], b[2];
+  };
+  Frag f0, f1;
   // Diagonal tiles are computed in full (their masked half is ~2% of the MFMA
   // work of a causal layer); a per-MFMA skip would break the inner loop into
   // branches that serialise every LDS read with its MFMA.
   const uint32_t xa = (uint32_t)swz_row(lr);  // swizzle of this lane's rows (32 t, 64 wr: same)
-  // hook(ks) runs at the start of k-step ks: the loads of the next chunk are
-  // spread over the k-steps (a burst after the barrier stalls the wave at issue)
-  auto compute = [&](int ch, auto hook) {
-    const uint16_t* A = lds + (ch % NSTAGE) * 2 * kStage;
-    const uint16_t* Bm = A + kStage;
+  auto read_step = [&](int stage, int ks, Frag& f) __attribute__((always_inline)) {
+    const uint16_t* A = lds + stage * kStage;
+    const uint16_t* Bm = A + NSTAGE * kStage;
+    const uint32_t coff = (uint32_t)((((2 * ks + lh) ^ xa)) << 3);  // elements
 #pragma unroll
-    for (int ks = 0; ks < KC / 16; ++ks) {
-      hook(ks);
-      const uint32_t coff = (uint32_t)((((2 * ks + lh) ^ xa)) << 3);  // elements
-      u32x4 bq[2];
+    for (int n = 0; n < 2; ++n)
+      f.b[n] = *(const u32x4*)(Bm + (64 * wr + 32 * n + lr) * KC + coff);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      f.a[t] = *(const u32x4*)(A + (128 * wc + 32 * t + lr) * KC + coff);
+  };
+  auto mfma_step = [&](const Frag& f, bool zero) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int n = 0; n < 2; ++n)
-        bq[n] = *(const u32x4*)(Bm + (64 * wr + 32 * n + lr) * KC + coff);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const u32x4 ak = *(const u32x4*)(A + (128 * wc + 32 * t + lr) * KC + coff);
-#pragma unroll
-        for (int n = 0; n < 2; ++n) acc[t][n] = mfma32(as_bf16x8(ak), as_bf16x8(bq[n]), acc[t][n]);
-      }
-    }
-    // Issue order per chunk: the 6 reads of k-step 0, then for each k-step its
-    // 8 MFMAs with the 6 reads of the next k-step interleaved.
-    __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
-#pragma unroll
-    for (int kk = 0; kk + 1 < KC / 16; ++kk) {
-#pragma unroll
-      for (int i = 0; i < 6; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+        acc[t][n] = mfma32(as_bf16x8(f.a[t]), as_bf16x8(f.b[n]), zero ? f32x16{} : acc[t][n]);
   };
-  static_assert(kDmaPerOp == KC / 16, "one load pair per k-step");
+  // issue order of one k-step: the next k-step's 6 reads between its 8 MFMAs
+  auto step_order = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+  };
+  // One chunk, already in LDS stage STAGE with its k-step 0 in f0. Before the
+  // last k-step's MFMAs (whose operands are in registers by then) the wave
+  // waits for its loads of the next chunk and the barrier makes everyone's
+  // visible and ends all reads of this stage; the next chunk's k-step 0 is
+  // then read under the last k-step's MFMAs, so no wave starts a chunk
+  // without operands. early() and late() issue the second half of the next
+  // chunk's loads and the first half of those of the chunk after it.
+  // Against waiting at the chunk's start (both waves of a SIMD then read 6 KB
+  // before their first MFMA): 4.10 -> 4.03 ms at 128K tokens, 32/8 heads,
+  // S = 16, and 4.76 -> 4.61 ms at 64K, S = 4 (finalize included). The rest
+  // is the power limit: MFMA pipes 68 % busy at 1.50 GHz, where a library GEMM
+  // of 16384^3 keeps them 90 % busy at 1.55 GHz.
+  auto chunk = [&](auto stage_tag, bool zero, auto early, auto late) __attribute__((always_inline)) {
+    constexpr int STAGE = decltype(stage_tag)::value;
+    early();
+    read_step(STAGE, 1, f1);
+    mfma_step(f0, zero);
+    step_order();
+    __builtin_amdgcn_sched_barrier(0);
+    read_step(STAGE, 2, f0);
+    mfma_step(f1, false);
+    step_order();
+    __builtin_amdgcn_sched_barrier(0);
+    read_step(STAGE, 3, f1);
+    mfma_step(f0, false);
+    step_order();
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt<0>();
+    barrier_nofence();
+    late();
+    read_step(STAGE ^ 1, 0, f0);
+    mfma_step(f1, false);
+    step_order();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_assert(KC == 64 && kDmaPerOp == 4 && NSTAGE == 2, "the chunk's four k-steps");
 
   auto epilogue = [&](const int h, const int R0, const int c0) {
     // ---- epilogue per 32-row slab n: this lane owns reduced row R and 64 of the
@@ -202,13 +240,13 @@ __global__ __launch_bounds__(kThreads, 1) void score_partials(
       const int Rslab = R0 + 64 * wr + 32 * n;
       if ((CAUSAL && csub + 127 > Rslab) || csub + 127 >= NR) {
         asm volatile("");
+        // last valid column of this row, relative to the lane's first one
+        const int last = (CAUSAL ? min(R, NR - 1) : NR - 1) - csub - 4 * lh;
   #pragma unroll
         for (int t = 0; t < 4; ++t) {
   #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int c = csub + 32 * t + 8 * (r >> 2) + 4 * lh + (r & 3);
-            if (c >= NR || (CAUSAL && c > R)) acc[t][n][r] = -INFINITY;
-          }
+          for (int r = 0; r < 16; ++r)
+            if (32 * t + 8 * (r >> 2) + (r & 3) > last) acc[t][n][r] = -INFINITY;
         }
       }
       // max of the raw products (the scale is positive), then every term as
@@ -308,27 +346,36 @@ __global__ __launch_bounds__(kThreads, 1) void score_partials(
   load_tile(lo + k8);
 #pragma unroll
   for (int i = 0; i < kDmaPerOp; ++i) dma_pair(0, i);
+  dma_pair(1, 0);
+  dma_pair(1, 1);
+  wait_vmcnt<4>();  // chunk 0 has landed
+  barrier_nofence();
+  read_step(0, 0, f0);
+  using Even = std::integral_constant<int, 0>;
+  using Odd = std::integral_constant<int, 1>;
   for (int it = k8; it < cnt_x; it += nper) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int n = 0; n < 2; ++n) acc[t][n] = f32x16{};
-    // Step ch: this wave's loads of chunk ch have landed; the barrier makes
-    // everyone's visible and ends every wave's reads of chunk ch - 1, whose
-    // stage now receives chunk ch + 1, one pair per k-step of compute(ch).
-    for (int ch = 0; ch + 1 < NCH; ++ch) {
-      wait_vmcnt<0>();
-      barrier_nofence();
-      compute(ch, [&](int ks) { dma_pair(ch + 1, ks); });
-    }
-    wait_vmcnt<0>();
-    barrier_nofence();
-    // Chunk 0 of the next tile goes to stage 0 (chunk NCH - 2's, finished by
-    // everyone) during the last chunk; after the last tile the same tile's
-    // chunk 0 is loaded again (in bounds, never read).
+    // Chunks in pairs (stage 0, stage 1). The last pair switches to the next
+    // tile between its chunks: that tile's chunk 0 and half of its chunk 1
+    // are then loaded before the epilogue. After the last tile the same
+    // tile's chunks are loaded again (in bounds, never used).
     const int h_done = th, R0_done = tR0, c0_done = tc0;
-    if (it + nper < cnt_x) load_tile(lo + it + nper);
-    compute(NCH - 1, [&](int ks) { dma_pair(0, ks); });
+    auto pair = [&](int ch, bool zero) __attribute__((always_inline)) {
+      chunk(Even{}, zero, [&] { dma_pair(ch + 1, 2); dma_pair(ch + 1, 3); },
+            [&] { dma_pair(ch + 2, 0); dma_pair(ch + 2, 1); });
+      chunk(Odd{}, false, [&] { dma_pair(ch + 2, 2); dma_pair(ch + 2, 3); },
+            [&] { dma_pair(ch + 3, 0); dma_pair(ch + 3, 1); });
+    };
+    if constexpr (NCH > 2) pair(0, true);
+#pragma unroll 1
+    for (int ch = 2; ch + 2 < NCH; ch += 2) pair(ch, false);
+    chunk(Even{}, NCH == 2, [&] { dma_pair(NCH - 1, 2); dma_pair(NCH - 1, 3); },
+          [&] {
+            if (it + nper < cnt_x) load_tile(lo + it + nper);
+            dma_pair(0, 0);
+            dma_pair(0, 1);
+          });
+    chunk(Odd{}, false, [&] { dma_pair(0, 2); dma_pair(0, 3); },
+          [&] { dma_pair(1, 0); dma_pair(1, 1); });
     epilogue(h_done, R0_done, c0_done);
   }
   wait_vmcnt<0>();  // the last loads land before the LDS is released

@@ -9,7 +9,7 @@
 namespace xattn {
 
 constexpr int kTsub = 128;      // reduced-column sub-tile owning one (max, sum) per row
-constexpr int kStatMax = 2048;  // (row, sub-tile) stats staged in LDS (16 KB) when they fit
+constexpr int kFactorMax = 4096;  // (row, sub-tile) factors staged in LDS (16 KB) at a time
 constexpr int kFinUnroll = 4;   // independent 16-byte partial-sum loads per thread
 constexpr int kFinThreads = 256;
 
@@ -37,21 +37,10 @@ __host__ __device__ inline size_t stats_at(int h, int t, int R, int NR, int NT, 
                 : head + (size_t)t * NR + R;
 }
 
-__device__ __forceinline__ float fin_wave_max(float x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-  return x;
-}
-__device__ __forceinline__ float fin_wave_sum(float x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-  return x;
-}
-
 // LDS of one finalisation (one workgroup of kFinThreads per row).
 struct FinalizeLds {
-  float mR[kBlock], ilR[kBlock];
-  float sm[kStatMax], sl[kStatMax];  // sm[t * nrb + r]: m, then the factor f
+  float red[2][kFinThreads];  // per wave (or pair of waves) and reduced row: max, sum
+  float f[kFactorMax];        // f[(t - t0) * nrb + r]
 };
 
 // Block scores of row (h, b), nrb = B/S reduced rows R = b nrb + r and tn
@@ -60,105 +49,110 @@ struct FinalizeLds {
 //   f[r][t] = 2^(m[t][R] - m_R) / l_R,
 //   out[j] = (1/nrb) sum_r part[j][r] f[r][t(j)]   for the candidates j,
 //   out[j] = 0 for the other j < NB (causal: j > b).
-// The (r, t) stats are read r-fastest (the nrb rows of one sub-tile are
-// adjacent in memory) into LDS; one wave per reduced row reduces them in a
-// fixed order. The row's partial-sum slab [j][r] is streamed as float4 (or
-// float2 when nrb = 2), kFinUnroll loads in flight per thread; the nrb / 4
-// lanes of one block then reduce with shuffles in a fixed order. Rows whose
-// stats exceed the LDS stage use the same arithmetic with the stats read from
-// global memory. Called by all kFinThreads threads of the workgroup.
+// Thread i reads the stats of reduced row i mod nrb, sub-tiles i / nrb + u *
+// (kFinThreads / nrb): the nrb rows of one sub-tile are adjacent in memory.
+// The kFinThreads / nrb threads of a row are combined by shuffles inside a
+// wave and through LDS across waves, in a fixed order. The
+// factors are then staged kFactorMax at a time, and the part of the row's
+// partial-sum slab [j][r] that they scale is streamed as float4 (or float2
+// when nrb = 2), kFinUnroll loads in flight per thread; the nrb / 4 lanes of
+// one block reduce with shuffles in a fixed order. Bound by the slab's bytes
+// at every stride: at small strides a row has more factors than fit (S = 4:
+// 4096 at 64K tokens, S = 1: 65536), and reading four stats and evaluating
+// four exponentials per float4 instead took 0.420 ms at 64K, 32/8 heads,
+// S = 4 (0.54 GB of partial sums). Called by all kFinThreads threads.
 template <bool CAUSAL>
 __device__ __forceinline__ void finalize_row(const float* __restrict__ part,
                                              const float2* __restrict__ stats, int NR, int NB,
                                              int NT, int nrb, int h, int b,
                                              float* __restrict__ out, FinalizeLds& L) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x;
   const int ncand = CAUSAL ? b + 1 : NB;
   const int tn = CAUSAL ? (b * nrb) / kTsub + 1 : NT;  // sub-tiles of this row's stats
   const int R0 = b * nrb;
-  auto st = [&](int t, int r) -> float2 { return stats[stats_at(h, t, R0 + r, NR, NT, CAUSAL)]; };
-  const bool staged = nrb * tn <= kStatMax;
-  if (staged) {
-    for (int i = tid; i < nrb * tn; i += kFinThreads) {
-      const int t = i / nrb, r = i - t * nrb;
-      const float2 v = st(t, r);
-      L.sm[i] = v.x;
-      L.sl[i] = v.y;
-    }
-    __syncthreads();
-  }
-  for (int r = wv; r < nrb; r += kFinThreads / 64) {
-    float m = -INFINITY;
-    for (int t = lane; t < tn; t += 64) m = fmaxf(m, staged ? L.sm[t * nrb + r] : st(t, r).x);
-    m = fin_wave_max(m);
-    float l = 0.f;
-    for (int t = lane; t < tn; t += 64) {
-      const float2 v = staged ? make_float2(L.sm[t * nrb + r], L.sl[t * nrb + r]) : st(t, r);
-      l += v.y * fast_exp2(v.x - m);
-    }
-    l = fin_wave_sum(l);
-    if (lane == 0) {
-      L.mR[r] = m;
-      L.ilR[r] = 1.f / l;
-    }
-  }
-  __syncthreads();
-  if (staged) {
-    for (int i = tid; i < nrb * tn; i += kFinThreads) {
-      const int r = i % nrb;
-      L.sm[i] = fast_exp2(L.sm[i] - L.mR[r]) * L.ilR[r];
-    }
-    __syncthreads();
-  }
-  auto factor = [&](int r, int t) -> float {
-    return staged ? L.sm[t * nrb + r] : fast_exp2(st(t, r).x - L.mR[r]) * L.ilR[r];
+  const int r_own = tid % nrb, t_own = tid / nrb, tstep = kFinThreads / nrb;
+  auto st = [&](int t) -> float2 {
+    return stats[stats_at(h, t, R0 + r_own, NR, NT, CAUSAL)];
   };
+  // the threads of one reduced row: lanes nrb apart in a wave (nrb < 64), then
+  // the groups of max(nrb, 64) threads
+  const int group = nrb > 64 ? nrb : 64, g_own = tid / group;
+  const bool writes = tid % group < nrb;
+  float m = -INFINITY;
+  for (int t = t_own; t < tn; t += tstep) m = fmaxf(m, st(t).x);
+  for (int off = 32; off >= nrb; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+  if (writes) L.red[0][g_own * nrb + r_own] = m;
+  __syncthreads();
+  m = L.red[0][r_own];
+  for (int g = 1; g < kFinThreads / group; ++g) m = fmaxf(m, L.red[0][g * nrb + r_own]);
+  float l = 0.f;
+  for (int t = t_own; t < tn; t += tstep) {
+    const float2 v = st(t);
+    l += v.y * fast_exp2(v.x - m);
+  }
+  for (int off = 32; off >= nrb; off >>= 1) l += __shfl_xor(l, off);
+  if (writes) L.red[1][g_own * nrb + r_own] = l;
+  __syncthreads();
+  l = L.red[1][r_own];
+  for (int g = 1; g < kFinThreads / group; ++g) l += L.red[1][g * nrb + r_own];
+  const float il = 1.f / l;
 
   const float inv_nrb = 1.f / (float)nrb;
   const float* pb = part + part_row(h, b, NB, CAUSAL) * nrb;  // this row's slab [j][r]
-  if (nrb >= 4) {
-    // chunk q = 4 consecutive floats = rows 4 (q % (nrb/4)) .. +3 of block q / (nrb/4)
-    const int cpb = nrb / 4;  // chunks (lanes) per block, a power of two <= 32
-    const int nq = ncand * cpb;
-    const float4* p4 = (const float4*)pb;
-    for (int q0 = 0; q0 < nq; q0 += kFinThreads * kFinUnroll) {
-      float4 v[kFinUnroll];
+  const int tchunk = kFactorMax / nrb;
+  const int jper = kTsub / nrb;  // key blocks per sub-tile
+  for (int t0 = 0; t0 < tn; t0 += tchunk) {
+    const int t1 = min(t0 + tchunk, tn);
+    for (int t = t0 + t_own; t < t1; t += tstep)
+      L.f[(t - t0) * nrb + r_own] = fast_exp2(st(t).x - m) * il;
+    __syncthreads();
+    const int j_lo = t0 * jper, j_hi = min(t1 * jper, ncand);
+    auto factor = [&](int r, int t) -> float { return L.f[(t - t0) * nrb + r]; };
+    if (nrb >= 4) {
+      // chunk q = 4 consecutive floats = rows 4 (q % (nrb/4)) .. +3 of block q / (nrb/4)
+      const int cpb = nrb / 4;  // chunks (lanes) per block, a power of two <= 32
+      const int nq = j_hi * cpb;
+      const float4* p4 = (const float4*)pb;
+      for (int q0 = j_lo * cpb; q0 < nq; q0 += kFinThreads * kFinUnroll) {
+        float4 v[kFinUnroll];
 #pragma unroll
-      for (int u = 0; u < kFinUnroll; ++u) {
-        const int q = q0 + kFinThreads * u + tid;
-        v[u] = q < nq ? p4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+        for (int u = 0; u < kFinUnroll; ++u) {
+          const int q = q0 + kFinThreads * u + tid;
+          v[u] = q < nq ? p4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
 #pragma unroll
-      for (int u = 0; u < kFinUnroll; ++u) {
-        const int q = q0 + kFinThreads * u + tid;
-        const int j = q / cpb, r0 = 4 * (q % cpb);
-        const int t = (j * nrb) / kTsub;
-        float acc = 0.f;
-        if (q < nq)
-          acc = v[u].x * factor(r0, t) + v[u].y * factor(r0 + 1, t) +
-                v[u].z * factor(r0 + 2, t) + v[u].w * factor(r0 + 3, t);
-        for (int off = cpb / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-        if (q < nq && (q % cpb) == 0) out[j] = acc * inv_nrb;
-      }
-    }
-  } else {  // nrb == 2: one float2 per block
-    const float2* p2 = (const float2*)pb;
-    for (int j0 = 0; j0 < ncand; j0 += kFinThreads * kFinUnroll) {
-      float2 v[kFinUnroll];
-#pragma unroll
-      for (int u = 0; u < kFinUnroll; ++u) {
-        const int j = j0 + kFinThreads * u + tid;
-        v[u] = j < ncand ? p2[j] : make_float2(0.f, 0.f);
-      }
-#pragma unroll
-      for (int u = 0; u < kFinUnroll; ++u) {
-        const int j = j0 + kFinThreads * u + tid;
-        if (j < ncand) {
+        for (int u = 0; u < kFinUnroll; ++u) {
+          const int q = q0 + kFinThreads * u + tid;
+          const int j = q / cpb, r0 = 4 * (q % cpb);
           const int t = (j * nrb) / kTsub;
-          out[j] = (v[u].x * factor(0, t) + v[u].y * factor(1, t)) * inv_nrb;
+          float acc = 0.f;
+          if (q < nq)
+            acc = v[u].x * factor(r0, t) + v[u].y * factor(r0 + 1, t) +
+                  v[u].z * factor(r0 + 2, t) + v[u].w * factor(r0 + 3, t);
+          for (int off = cpb / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+          if (q < nq && (q % cpb) == 0) out[j] = acc * inv_nrb;
+        }
+      }
+    } else {  // nrb == 2: one float2 per block
+      const float2* p2 = (const float2*)pb;
+      for (int j0 = j_lo; j0 < j_hi; j0 += kFinThreads * kFinUnroll) {
+        float2 v[kFinUnroll];
+#pragma unroll
+        for (int u = 0; u < kFinUnroll; ++u) {
+          const int j = j0 + kFinThreads * u + tid;
+          v[u] = j < j_hi ? p2[j] : make_float2(0.f, 0.f);
+        }
+#pragma unroll
+        for (int u = 0; u < kFinUnroll; ++u) {
+          const int j = j0 + kFinThreads * u + tid;
+          if (j < j_hi) {
+            const int t = (j * nrb) / kTsub;
+            out[j] = (v[u].x * factor(0, t) + v[u].y * factor(1, t)) * inv_nrb;
+          }
         }
       }
     }
+    if (t1 < tn) __syncthreads();  // the factors are replaced
   }
   for (int j = ncand + tid; j < NB; j += kFinThreads) out[j] = 0.f;  // not candidates
 }

@@ -18,6 +18,7 @@
 // normalises, and averages the B/S reduced rows of each query block.
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "score_rows.h"
@@ -381,6 +382,291 @@ __global__ __launch_bounds__(kThreads, 1) void score_partials(
   wait_vmcnt<0>();  // the last loads land before the LDS is released
 }
 
+// Small problems: the same partial sums in tiles of 128 columns (one sub-tile)
+// x RT rows, one workgroup of 4 waves each. A few 256 x 256 tiles leave most
+// CUs idle, and each is a serial chain of chunks as long as the load latency;
+// these tiles are 4 to 16 times as many, and a ring of 4 to 6 LDS stages keeps
+// 80 to 120 KB of loads in flight per CU (a chunk of a 128 x 32 tile takes
+// 0.22 us alone, one of a 256 x 256 tile 1.05 us). Every product is added in
+// the same order as in score_partials; only a row's sum l and the masses of
+// blocks wider than a wave's columns are added in another one.
+template <int RT>
+struct SmallTile {
+  static constexpr int kWc = RT >= 128 ? 2 : 4;        // waves along the columns
+  static constexpr int kTn = TSUB / 32 / kWc;          // 32-column tiles per wave
+  static constexpr int kRn = RT / 32 / (4 / kWc);      // 32-row tiles per wave
+  static constexpr int kRows = TSUB + RT;              // LDS rows per stage (K~, then Q~)
+  static constexpr int kIpw = kRows / kDmaRows / 4;    // load instructions per wave per chunk
+  static constexpr int kStages = RT >= 128 ? 4 : 6;      // even; 120 - 144 KB of LDS
+  static constexpr int kStageElems = kRows * KC;
+};
+
+// Tiles of a head: row tile rt has (rt RT) / 128 + 1 column tiles when causal.
+template <int RT, bool CAUSAL>
+__host__ __device__ inline int small_tiles(int NR) {
+  const int nrt = ceil_div(NR, RT), k = TSUB / RT, nct = ceil_div(NR, TSUB);
+  if (!CAUSAL) return nrt * nct;
+  const int g = (nrt - 1) / k;
+  return k * (g * (g + 1) / 2) + (nrt - g * k) * (g + 1);
+}
+
+// f(integral_constant<int, I>) for every I of the sequence, in order.
+template <int... I, typename F>
+__device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+template <int NRB, bool CAUSAL, int RT>
+__global__ __launch_bounds__(256, 1) void score_partials_small(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int hq, int hkv, int L,
+    int NR, int NB, int NT, int tiles_per_head, int n_work, float scale_log2,
+    SubRowPairing pairing, float* __restrict__ part, float2* __restrict__ stats) {
+  using T = SmallTile<RT>;
+  constexpr int S = kBlock / NRB, KD = S * kHeadDim, NCH = KD / KC;
+  constexpr int kAhead = NCH < T::kStages ? NCH : T::kStages;  // chunks in flight
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[T::kStages * T::kStageElems];
+  __shared__ float red_m[4][RT], red_s[4][RT];
+
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wc = wv % T::kWc, wr = wv / T::kWc;
+
+  const int x8 = blockIdx.x % kNumXcd, k8 = blockIdx.x / kNumXcd;
+  const int per = n_work / kNumXcd, rem = n_work % kNumXcd;
+  if (k8 >= per + (x8 < rem ? 1 : 0)) return;  // uniform
+  const int w = x8 * per + (x8 < rem ? x8 : rem) + k8;
+  const int G = hq / hkv;
+  const int hh = w % G, rest = w / G;
+  const int tile = rest % tiles_per_head, gidx = rest / tiles_per_head;
+  const int h = __builtin_amdgcn_readfirstlane((gidx / hkv) * hq + (gidx % hkv) * G + hh);
+  int rt, ct;
+  if (CAUSAL) {
+    constexpr int kk = TSUB / RT;
+    int g, unused;
+    tri_decode(tile / kk, g, unused);
+    const int r = tile - kk * (g * (g + 1) / 2);
+    rt = g * kk + r / (g + 1);
+    ct = r % (g + 1);
+  } else {
+    rt = tile / NT;
+    ct = tile % NT;
+  }
+  const int R0 = __builtin_amdgcn_readfirstlane(rt * RT);
+  const int c0 = __builtin_amdgcn_readfirstlane(ct * TSUB);
+  const uint16_t* Qh = q + (size_t)h * L * kHeadDim;
+  const uint16_t* Kg = k + (size_t)__builtin_amdgcn_readfirstlane(gidx) * L * kHeadDim;
+
+  // load i of this wave fills LDS rows kDmaRows (kIpw wv + i) .. of a stage;
+  // rows beyond NR are clamped to NR - 1 (results masked / not stored)
+  uint32_t off[T::kIpw];
+#pragma unroll
+  for (int i = 0; i < T::kIpw; ++i) {
+    const int r = kDmaRows * (T::kIpw * wv + i) + lane / kCPR;
+    const int c = (lane & (kCPR - 1)) ^ swz_row(r);
+    const int src = r < TSUB ? min(c0 + r, NR - 1) : min(R0 + r - TSUB, NR - 1);
+    off[i] = (uint32_t)(((size_t)src * KD + c * 8) * 2);
+  }
+  const uint32_t lds0 = XATTN_LDS_ADDR(lds);
+  const int qsub_lane = pairing.q[lane < S ? lane : 0];
+  auto load_chunk = [&](int ch) __attribute__((always_inline)) {
+    const int kap0 = ch * KC;
+    const uint16_t* baseA = Kg + kap0;
+    const uint16_t* baseB =
+        Qh + __builtin_amdgcn_readlane(qsub_lane, kap0 / kHeadDim) * kHeadDim + kap0 % kHeadDim;
+    const uint32_t st = lds0 + (uint32_t)((ch % T::kStages) * T::kStageElems * 2);
+#pragma unroll
+    for (int i = 0; i < T::kIpw; ++i) {
+      const int row = kDmaRows * (T::kIpw * wv + i);  // uniform
+      dma16(row < TSUB ? baseA : baseB, off[i], st + (uint32_t)(row * KC * 2));
+    }
+  };
+
+  f32x16 acc[T::kTn][T::kRn];
+#pragma unroll
+  for (int t = 0; t < T::kTn; ++t)
+#pragma unroll
+    for (int n = 0; n < T::kRn; ++n) acc[t][n] = f32x16{};
+  const uint32_t xa = (uint32_t)swz_row(lr);
+  struct Frags {  // operands of one chunk
+    u32x4 a[KC / 16][T::kTn], b[KC / 16][T::kRn];
+  };
+  Frags f0, f1;
+  auto read_chunk = [&](int ch, Frags& f) __attribute__((always_inline)) {
+    const uint16_t* A = lds + (ch % T::kStages) * T::kStageElems;
+    const uint16_t* Bm = A + TSUB * KC;
+#pragma unroll
+    for (int ks = 0; ks < KC / 16; ++ks) {
+      const uint32_t coff = (uint32_t)((((2 * ks + lh) ^ xa)) << 3);
+#pragma unroll
+      for (int t = 0; t < T::kTn; ++t)
+        f.a[ks][t] = *(const u32x4*)(A + (32 * (T::kTn * wc + t) + lr) * KC + coff);
+#pragma unroll
+      for (int n = 0; n < T::kRn; ++n)
+        f.b[ks][n] = *(const u32x4*)(Bm + (32 * (T::kRn * wr + n) + lr) * KC + coff);
+    }
+  };
+  auto mfma_chunk = [&](const Frags& f) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < KC / 16; ++ks)
+#pragma unroll
+      for (int t = 0; t < T::kTn; ++t)
+#pragma unroll
+        for (int n = 0; n < T::kRn; ++n)
+          acc[t][n] = mfma32(as_bf16x8(f.a[ks][t]), as_bf16x8(f.b[ks][n]), acc[t][n]);
+  };
+
+  for (int ch = 0; ch < kAhead; ++ch) load_chunk(ch);
+  wait_vmcnt<(kAhead - 1) * T::kIpw>();
+  barrier_nofence();
+  read_chunk(0, f0);
+  // Step ch: chunk ch + 1 has landed for this wave; the barrier makes
+  // everyone's visible and ends every wave's reads of chunk ch, whose stage
+  // receives chunk ch + kAhead; chunk ch + 1 is read while chunk ch's MFMAs run.
+  auto step = [&](int ch, const Frags& f, Frags& fn) __attribute__((always_inline)) {
+    wait_vmcnt<(kAhead - 2) * T::kIpw>();
+    barrier_nofence();
+    load_chunk(ch + kAhead);
+    read_chunk(ch + 1, fn);
+    mfma_chunk(f);
+  };
+  static_assert(kAhead % 2 == 0 && NCH % 2 == 0, "steps come in pairs");
+#pragma unroll 1
+  for (int ch = 0; ch < NCH - kAhead; ch += 2) {
+    step(ch, f0, f1);
+    step(ch + 1, f1, f0);
+  }
+  for_each_index(std::make_integer_sequence<int, kAhead>{}, [&](auto i) {
+    constexpr int I = decltype(i)::value;
+    if constexpr (I + 1 < kAhead) {
+      wait_vmcnt<(kAhead - 2 - I) * T::kIpw>();
+      barrier_nofence();
+      read_chunk(NCH - kAhead + I + 1, I % 2 ? f0 : f1);
+    }
+    mfma_chunk(I % 2 ? f1 : f0);
+  });
+
+  // ---- epilogue: lane (lr, lh) holds, per 32 x 32 tile, row lr and columns
+  // 8 g + 4 lh + [0, 4); a row's 128 columns span the kWc column waves.
+  const int cw = 32 * T::kTn * wc;  // this wave's first column in the tile
+#pragma unroll
+  for (int n = 0; n < T::kRn; ++n) {
+    const int rl = 32 * (T::kRn * wr + n) + lr;  // row in the tile
+    const int R = R0 + rl;
+    const int last = (CAUSAL ? min(R, NR - 1) : NR - 1) - c0 - cw - 4 * lh;
+    if (last < 32 * T::kTn) {
+#pragma unroll
+      for (int t = 0; t < T::kTn; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (32 * t + 8 * (r >> 2) + (r & 3) > last) acc[t][n][r] = -INFINITY;
+    }
+    float mloc = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < T::kTn; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, acc[t][n][r]);
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+    if (lh == 0) red_m[wc][rl] = mloc;
+  }
+  __syncthreads();
+  float m_row[T::kRn];
+#pragma unroll
+  for (int n = 0; n < T::kRn; ++n) {
+    const int rl = 32 * (T::kRn * wr + n) + lr;
+    const int R = R0 + rl;
+    float m = red_m[0][rl];
+#pragma unroll
+    for (int u = 1; u < T::kWc; ++u) m = fmaxf(m, red_m[u][rl]);
+    m *= scale_log2;
+    m_row[n] = m;
+    const float mref = (m == -INFINITY) ? 0.f : m;
+    const bool rvalid = R < NR;
+    const int Rv = rvalid ? R : 0;
+    const int qb = Rv / NRB;
+    float* pcol = part + part_row(h, qb, NB, CAUSAL) * NRB + (Rv % NRB);
+    auto keep = [&](int j) { return rvalid && j < NB && (!CAUSAL || j <= qb); };
+    float lloc = 0.f;
+#pragma unroll
+    for (int t = 0; t < T::kTn; ++t) {
+      const int j0 = (c0 + cw + 32 * t) / NRB;
+      float gsum[4];
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        float sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float p = fast_exp2(fmaf(acc[t][n][4 * g4 + e], scale_log2, -mref));
+          acc[t][n][4 * g4 + e] = p;
+          sum += p;
+        }
+        gsum[g4] = sum;
+        lloc += sum;
+      }
+      if constexpr (NRB == 8) {  // group g is block g
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          const float tot = half_pair_sum(gsum[x], gsum[x + 2]);
+          const int j = j0 + 2 * lh + x;
+          if (keep(j)) pcol[(size_t)j * NRB] = tot;
+        }
+      } else if constexpr (NRB == 16) {
+        const float tot = half_pair_sum(gsum[0] + gsum[1], gsum[2] + gsum[3]);
+        if (keep(j0 + lh)) pcol[(size_t)(j0 + lh) * NRB] = tot;
+      } else if constexpr (NRB == 32) {
+        const float s0 = gsum[0] + gsum[1] + gsum[2] + gsum[3];
+        const float tot = half_pair_sum(s0, s0);
+        if (lh == 0 && keep(j0)) pcol[(size_t)j0 * NRB] = tot;
+      } else if constexpr (NRB == 4) {
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const int j = j0 + 2 * g4 + lh;
+          if (keep(j)) pcol[(size_t)j * NRB] = gsum[g4];
+        }
+      } else if constexpr (NRB == 2) {
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const int j = j0 + 4 * g4 + 2 * lh;
+          if (keep(j)) pcol[(size_t)j * NRB] = acc[t][n][4 * g4] + acc[t][n][4 * g4 + 1];
+          if (keep(j + 1))
+            pcol[(size_t)(j + 1) * NRB] = acc[t][n][4 * g4 + 2] + acc[t][n][4 * g4 + 3];
+        }
+      }
+    }
+    const float l = lloc + __shfl_xor(lloc, 32);
+    if (lh == 0) red_s[wc][rl] = l;
+  }
+  __syncthreads();
+  // row totals over the column waves; blocks wider than a wave's columns
+  // (NRB = 64, 128) are sums of the same per-wave totals
+  if (wc == 0 && lh == 0) {
+#pragma unroll
+    for (int n = 0; n < T::kRn; ++n) {
+      const int rl = 32 * (T::kRn * wr + n) + lr;
+      const int R = R0 + rl;
+      float l = red_s[0][rl];
+#pragma unroll
+      for (int u = 1; u < T::kWc; ++u) l += red_s[u][rl];
+      if (R < NR && (!CAUSAL || R >= c0))
+        stats[stats_at(h, c0 / TSUB, R, NR, NT, CAUSAL)] = make_float2(m_row[n], l);
+      if constexpr (NRB >= 64) {
+        constexpr int kPer = NRB * T::kWc / TSUB;  // column waves per block
+        if (R < NR) {
+          const int qb = R / NRB;
+          float* pcol = part + part_row(h, qb, NB, CAUSAL) * NRB + R % NRB;
+#pragma unroll
+          for (int x = 0; x < T::kWc / kPer; ++x) {
+            const int j = c0 / NRB + x;
+            float tot = 0.f;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) tot += red_s[x * kPer + u][rl];
+            if (j < NB && (!CAUSAL || j <= qb)) pcol[(size_t)j * NRB] = tot;
+          }
+        }
+      }
+    }
+  }
+}
+
 // One workgroup (4 waves) per (query head, query block) row: the row's
 // scores from its partial sums and tile statistics (finalize_row).
 template <bool CAUSAL>
@@ -413,6 +699,19 @@ int persistent_workgroups() {
   return n;
 }
 
+template <int NRB, bool CAUSAL, int RT>
+hipError_t launch_small(const void* q, const void* k, const XattnShape& s,
+                        const SubRowPairing& pr, float scale_log2, float* part, float* stats,
+                        hipStream_t st) {
+  const int NR = s.seq / (kBlock / NRB), tiles = small_tiles<RT, CAUSAL>(NR);
+  const int n_work = s.HQ() * tiles;
+  hipLaunchKernelGGL((score_partials_small<NRB, CAUSAL, RT>),
+                     dim3(ceil_div(n_work, kNumXcd) * kNumXcd), dim3(256), 0, st,
+                     (const uint16_t*)q, (const uint16_t*)k, s.hq, s.hkv, s.seq, NR, s.NB(),
+                     ceil_div(NR, TSUB), tiles, n_work, scale_log2, pr, part, (float2*)stats);
+  return hipGetLastError();
+}
+
 template <int NRB, bool CAUSAL>
 hipError_t launch_partials(const void* q, const void* k, const XattnShape& s,
                            const SubRowPairing& pr, float* part, float* stats, hipStream_t st) {
@@ -423,6 +722,30 @@ hipError_t launch_partials(const void* q, const void* k, const XattnShape& s,
   const float scale_log2 = kLog2e / (sqrtf((float)kHeadDim) * (float)S);
   // one resident workgroup per CU (128 KB of LDS each), a multiple of 8
   const int wgs = persistent_workgroups();
+  // The tile whose rounds over the chip (one workgroup per CU) cost least: a
+  // round takes a chunk's time (1.1 us per 64-deep chunk of 256 x 256, 0.52 of
+  // 128 x 128, 0.42 of 128 x 64, 0.30 of 128 x 32: a smaller tile moves more
+  // bytes per product but is done sooner) for each of its NCH chunks, and its
+  // start and epilogue (8 / 3.6 / 2.5 / 1.8 us), all measured with every CU
+  // busy. Small tiles win while the 256 x 256 ones leave CUs idle: xattn_score
+  // at 4K tokens, one head, S = 8 (3 such tiles): 29 -> 13 us; two 4736-token
+  // prompts of 8 heads, S = 16 (48): 46 -> 19 us; 8K, 32 heads, S = 16 (96):
+  // 51 -> 46 us. From about 200 on they lose: 8K, 32 heads, S = 8 (320): 66 us
+  // against 70 in 128 x 128 tiles.
+  constexpr int NCH = S * kHeadDim / KC;
+  const int heads = s.batch * s.hq;
+  auto rounds = [&](long long tiles_all) { return (tiles_all + wgs - 1) / wgs; };
+  const long long cost[4] = {
+      rounds(n_work) * (110 * NCH + 800),
+      rounds((long long)heads * small_tiles<128, CAUSAL>(NR)) * (52 * NCH + 360),
+      rounds((long long)heads * small_tiles<64, CAUSAL>(NR)) * (42 * NCH + 250),
+      rounds((long long)heads * small_tiles<32, CAUSAL>(NR)) * (30 * NCH + 180)};
+  int best = 0;
+  for (int i = 1; i < 4; ++i)
+    if (cost[i] < cost[best]) best = i;
+  if (best == 1) return launch_small<NRB, CAUSAL, 128>(q, k, s, pr, scale_log2, part, stats, st);
+  if (best == 2) return launch_small<NRB, CAUSAL, 64>(q, k, s, pr, scale_log2, part, stats, st);
+  if (best == 3) return launch_small<NRB, CAUSAL, 32>(q, k, s, pr, scale_log2, part, stats, st);
   hipLaunchKernelGGL((score_partials<NRB, CAUSAL>), dim3(wgs), dim3(kThreads), 0, st,
                      (const uint16_t*)q, (const uint16_t*)k, s.hq, s.hkv, s.seq, NR, NB, NT,
                      tiles, n_work, scale_log2, pr, part, (float2*)stats);

@@ -1,5 +1,6 @@
 // Step 3: block-sparse flash attention over the selected key blocks
 // (XAttention Fig. 1 right), and the dense mode (every candidate block).
+// attn_kernel is described here, attn_small_kernel for small problems below.
 //
 // One workgroup (4 waves) per (query head, query block of 128 rows); wave w
 // owns queries 32w .. 32w+31 of the block. Each listed 128-key block is
@@ -397,12 +398,264 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(
   attn_body<CAUSAL>(dense != 0, Ks, Vs, q, k, v, hq, hkv, L, NB, idx, cnt, scale_log2, o, lse);
 }
 
+// Small problems: 32 queries per workgroup instead of 128. Its 8 waves split
+// the keys, wave w taking keys 32 (w mod 4) .. +31 of the list entries of
+// parity w / 4, and are merged through LDS at the end. A grid of few
+// 128-query workgroups leaves most CUs idle, and each is a serial chain of
+// half-tiles as long as the load latency (1.3 us with 32 KB in flight); this
+// one has four times as many workgroups of half as many steps, 128 KB in
+// flight per CU. The next K and V (16 KB per wave) are loaded a step ahead
+// into registers, in rows, and pass through wave-private LDS for the operand
+// layouts, so no wave waits for another before the merge. It moves four times
+// the bytes per query of the 128-query kernel.
+constexpr int kSmallWaves = 8;
+constexpr int kSmallThreads = 64 * kSmallWaves;
+constexpr int kKeysW = 32;      // keys of a block per wave
+constexpr int kMergeRow = 132;  // floats per query row of the merge buffer: rows 4 banks apart
+
+template <bool CAUSAL>
+__global__ __launch_bounds__(kSmallThreads) void attn_small_kernel(
+    int dense, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+    const uint16_t* __restrict__ v, int hq, int hkv, int L, int NB, int n_work,
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, float scale_log2,
+    uint16_t* __restrict__ o, float* __restrict__ lse) {
+  // K and V tiles (16 KB per wave) during the loop, then the merge buffer
+  __shared__ __attribute__((aligned(1024))) float lds[kSmallWaves * 32 * kMergeRow];
+  __shared__ float red_m[kSmallWaves][32], red_l[kSmallWaves][32];
+
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int quarter = wv & 3, half = wv >> 2;
+  // The four 32-query parts of a query block are 8 workgroups apart, on one
+  // XCD, so that its L2 serves three of the four reads of a K/V block.
+  const int w = (blockIdx.x / 32) * 8 + blockIdx.x % 8;
+  const int sub = (blockIdx.x / 8) % 4;
+  if (w >= n_work) return;  // uniform
+  const int G = hq / hkv;
+  const int hh = w % G;
+  const int rest = w / G;
+  const int b = NB - 1 - rest % NB;
+  const int gidx = rest / NB;
+  const int h = (gidx / hkv) * hq + (gidx % hkv) * G + hh;
+  const uint16_t* Kg = k + (size_t)gidx * L * kHeadDim;
+  const uint16_t* Vg = v + (size_t)gidx * L * kHeadDim;
+  const int q0 = b * kBlock + 32 * sub;
+  const int qi = q0 + lr;
+
+  int n_kb;
+  const int32_t* list = nullptr;
+  if (dense) {
+    n_kb = CAUSAL ? b + 1 : NB;
+  } else {
+    n_kb = cnt[(size_t)h * NB + b];
+    n_kb = n_kb < 0 ? 0 : (n_kb > NB ? NB : n_kb);
+    list = idx + ((size_t)h * NB + b) * NB;
+  }
+  // as in attn_body: 64 entries of the list in one register, read in order
+  // (waited for at once, so that no step waits for the loads in flight)
+  auto list_chunk = [&](int c0) -> int {
+    const int i = c0 + lane;
+    return (!dense && i < n_kb) ? list[i] : 0;
+  };
+  int lchunk = 0, lreg = list_chunk(0);
+  asm volatile("" ::"v"(lreg));
+  auto block_at = [&](int it) -> int {  // calls come in increasing it
+    if (dense) return it;
+    if ((it & ~63) != lchunk) {
+      lchunk = it & ~63;
+      lreg = list_chunk(lchunk);
+      asm volatile("" ::"v"(lreg));
+    }
+    const int j = __builtin_amdgcn_readlane(lreg, it & 63);
+    return j < 0 ? 0 : (j >= NB ? NB - 1 : j);  // memory-safe on malformed lists
+  };
+
+  bf16x8 qb[8];
+  {
+    const uint16_t* Qr = q + ((size_t)h * L + qi) * kHeadDim + 8 * lh;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qb[s] = as_bf16x8(*(const u32x4*)(Qr + 16 * s));
+  }
+  f32x16 oacc[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) oacc[i] = f32x16{};
+  float m_ref = -INFINITY, l_run = 0.f;
+
+  // this wave's K and V tiles
+  uint16_t* Kw = (uint16_t*)lds + wv * (2 * kKeysW * kHeadDim);
+  uint16_t* Vw = Kw + kKeysW * kHeadDim;
+  u32x4 kr[8], vr[8];
+  const uint32_t row_lane = (uint32_t)((lane >> 4) * kHeadDim + (lane & 15) * 8);
+  // rows of this wave's quarter of a block, coalesced: load i holds rows 4 i + lane / 16
+  auto load_rows = [&](u32x4 (&r)[8], const uint16_t* base, int key) __attribute__((always_inline)) {
+    const uint16_t* src = base + (size_t)key * kHeadDim;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = *(const u32x4*)(src + row_lane + 4 * i * kHeadDim);
+  };
+  // this wave's step i is list entry 2 i + half; its first key (past the end: the last entry's)
+  const int n_steps = (n_kb - half + 1) / 2;
+  auto key_at = [&](int i) -> int {
+    const int it = 2 * i + half;
+    return block_at(it < n_kb ? it : n_kb - 1) * kBlock + kKeysW * quarter;
+  };
+  auto qk = [&]() __attribute__((always_inline)) -> f32x16 {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) *(u32x4*)&Kw[swz_k(4 * i + (lane >> 4), lane & 15)] = kr[i];
+    f32x16 s = f32x16{};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks)
+      s = mfma32(as_bf16x8(*(const u32x4*)&Kw[swz_k(lr, 2 * ks + lh)]), qb[ks], s);
+    return s;
+  };
+
+  const int tj = lane & 15, tg2 = (lane >> 4) & 1;
+  int key0 = 0, key1 = 0;  // first keys of steps i and i + 1 (uniform)
+  // Step i, scores in sc: QK^T of step i + 1 (into sn) beside the softmax of i, then PV of i.
+  // K(i + 1) and V(i) are in registers; K(i + 2) and V(i + 1) are loaded in their place.
+  auto step = [&](int i, f32x16& sc, f32x16& sn) __attribute__((always_inline)) {
+    const int key2 = key_at(i + 2);
+    const bool past = i >= n_steps;  // the second step of an odd last pair
+    if ((CAUSAL && key0 + kKeysW - 1 > q0) || past) {
+      asm volatile("");
+      // last visible key, relative to the lane's first one
+      const int last = past ? -1 : qi - key0 - 4 * lh;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (8 * (r >> 2) + (r & 3) > last) sc[r] = -INFINITY;
+    }
+    float mraw = sc[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mraw = fmaxf(mraw, sc[r]);
+    const float mt = half_max(mraw) * scale_log2;
+    if (__ballot(mt > m_ref + kRescaleSlack) != 0) {  // lazy rescaling, as in attn_body
+      const float m_new = fmaxf(m_ref, mt);
+      const float alpha = fast_exp2(m_ref - m_new);
+      m_ref = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) oacc[dt] *= alpha;
+    }
+    const float neg_m = (m_ref == -INFINITY) ? 0.f : -m_ref;
+    sn = qk();
+    load_rows(kr, Kg, key2);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) *(u32x4*)&Vw[swz_v(4 * r + (lane >> 4), lane & 15)] = vr[r];
+    load_rows(vr, Vg, key1);
+    uint32_t pk[8];
+    float ls = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {
+      const float p0 = fast_exp2(fmaf(sc[r], scale_log2, neg_m));
+      const float p1 = fast_exp2(fmaf(sc[r + 1], scale_log2, neg_m));
+      pk[r >> 1] = cvt_pk_bf16(p0, p1);
+      ls = sum_pk_bf16(pk[r >> 1], ls);
+    }
+    l_run += ls;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const bf16x8 pb = as_bf16x8(u32x4{pk[4 * u], pk[4 * u + 1], pk[4 * u + 2], pk[4 * u + 3]});
+      const int row = 16 * u + 4 * lh + (tj >> 2);
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) {
+        const int c = 4 * dt + 2 * tg2 + ((tj & 3) >> 1);
+        const int off = 4 * (tj & 1);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)&Vw[swz_v(row, c) + off]);
+        const s16x4 hi =
+            __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)&Vw[swz_v(row + 8, c) + off]);
+        const u32x2 lo2 = __builtin_bit_cast(u32x2, lo), hi2 = __builtin_bit_cast(u32x2, hi);
+        oacc[dt] = mfma32(as_bf16x8(u32x4{lo2[0], lo2[1], hi2[0], hi2[1]}), pb, oacc[dt]);
+      }
+    }
+    key0 = key1;
+    key1 = key2;
+    __builtin_amdgcn_sched_barrier(0);  // the loads stay in their step
+  };
+
+  if (n_steps > 0) {
+    key0 = key_at(0);
+    key1 = key_at(1);
+    load_rows(kr, Kg, key0);
+    load_rows(vr, Vg, key0);
+    __builtin_amdgcn_sched_barrier(0);
+    f32x16 sa = qk(), sb;
+    load_rows(kr, Kg, key1);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < n_steps; i += 2) {
+      step(i, sa, sb);
+      step(i + 1, sb, sa);
+    }
+  }
+
+  // ---- merge: the waves' (m, l) give the common reference and the total; each
+  // wave scales its accumulators to it, and they are added in wave order.
+  const float l_own = l_run + __shfl_xor(l_run, 32);
+  if (lh == 0) {
+    red_m[wv][lr] = m_ref;
+    red_l[wv][lr] = l_own;
+  }
+  __syncthreads();  // also: every wave is done with its tiles
+  float m_all = red_m[0][lr];
+#pragma unroll
+  for (int u = 1; u < kSmallWaves; ++u) m_all = fmaxf(m_all, red_m[u][lr]);
+  const float f = m_ref == -INFINITY ? 0.f : fast_exp2(m_ref - m_all);
+  float* mrow = lds + (wv * 32 + lr) * kMergeRow;
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4)
+      *(f32x4*)(mrow + 32 * dt + 8 * g4 + 4 * lh) =
+          f32x4{oacc[dt][4 * g4] * f, oacc[dt][4 * g4 + 1] * f, oacc[dt][4 * g4 + 2] * f,
+                oacc[dt][4 * g4 + 3] * f};
+  __syncthreads();
+  // thread -> query tid / 16, features 8 (tid mod 16) .. +7
+  const int qr = tid >> 4, f0 = 8 * (tid & 15);
+  float m_q = red_m[0][qr];
+#pragma unroll
+  for (int u = 1; u < kSmallWaves; ++u) m_q = fmaxf(m_q, red_m[u][qr]);
+  float l_q = 0.f;
+#pragma unroll
+  for (int u = 0; u < kSmallWaves; ++u) {
+    const float mu = red_m[u][qr];
+    l_q += mu == -INFINITY ? 0.f : red_l[u][qr] * fast_exp2(mu - m_q);
+  }
+  const float inv = l_q > 0.f ? 1.f / l_q : 0.f;
+  uint32_t out[4];
+#pragma unroll
+  for (int e = 0; e < 8; e += 4) {
+    f32x4 sum = *(const f32x4*)(lds + qr * kMergeRow + f0 + e);
+#pragma unroll
+    for (int u = 1; u < kSmallWaves; ++u)
+      sum += *(const f32x4*)(lds + (u * 32 + qr) * kMergeRow + f0 + e);
+    out[e / 2] = cvt_pk_bf16(sum[0] * inv, sum[1] * inv);
+    out[e / 2 + 1] = cvt_pk_bf16(sum[2] * inv, sum[3] * inv);
+  }
+  *(u32x4*)(o + ((size_t)h * L + q0 + qr) * kHeadDim + f0) = u32x4{out[0], out[1], out[2], out[3]};
+  if (lse != nullptr && (tid & 15) == 0)
+    lse[(size_t)h * L + q0 + qr] =
+        l_q > 0.f ? (m_q + __builtin_log2f(l_q)) * 0.69314718055994531f : -INFINITY;
+}
+
 template <bool CAUSAL>
 hipError_t launch_t(const void* q, const void* k, const void* v, const XattnShape& s,
                     const int32_t* idx, const int32_t* cnt, bool dense, void* o, float* lse,
                     hipStream_t st) {
   const int n_work = s.HQ() * s.NB();
   const float scale_log2 = kLog2e / sqrtf((float)kHeadDim);
+  // The small kernel while its workgroups (four per query block, one per CU)
+  // fit the chip once, or twice where rows are long: one head of 4K tokens,
+  // 54 % of the blocks (32 query blocks), 45 -> 25 us, all of them 61 -> 30 us;
+  // four heads of 2K (64) 26 -> 17.5 us; one head of 16K, 15 % (128), 51 -> 37
+  // us. Beyond, its four-fold traffic costs more than the idle CUs: eight heads
+  // of 2K (128 query blocks of short rows) 26.8 against 29.9 us, one head of
+  // 32K, 20 % (256), 116 against 125 us. Both modes choose alike, so that
+  // dense and full lists give the same bits.
+  if (n_work <= 64 || (n_work <= 128 && s.NB() >= 48)) {
+    hipLaunchKernelGGL((attn_small_kernel<CAUSAL>), dim3((n_work + 7) / 8 * 32), dim3(kSmallThreads), 0,
+                       st, dense ? 1 : 0, (const uint16_t*)q, (const uint16_t*)k,
+                       (const uint16_t*)v, s.hq, s.hkv, s.seq, s.NB(), n_work, idx, cnt,
+                       scale_log2, (uint16_t*)o, lse);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL((attn_kernel<CAUSAL>), dim3(n_work), dim3(kThreads), 0, st, dense ? 1 : 0,
                      (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, s.hq, s.hkv,
                      s.seq, s.NB(), idx, cnt, scale_log2, (uint16_t*)o, lse);

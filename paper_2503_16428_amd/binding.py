@@ -14,6 +14,7 @@ Tensor layouts (batch folded into heads when 3-D tensors are given):
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import numpy as np
@@ -180,13 +181,13 @@ def _check_outputs(q, dims: Dims, o=None, lse=None):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()  # argtypes turn it into a void*
 
 
 def _stream(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _need(t: torch.Tensor, dtype, name: str):
@@ -215,6 +216,19 @@ def forward_layout(dims: Dims, block: int, stride: int) -> dict:
     _check(lib().xattn_forward_layout(ctypes.byref(dims), block, stride,
                                       *[ctypes.byref(x) for x in v]))
     return dict(zip(("scores", "idx", "cnt", "scratch"), (x.value for x in v)))
+
+
+@functools.lru_cache(maxsize=256)
+def _forward_plan(batch, hq, hkv, seq, head_dim, causal, block, stride):
+    """(workspace bytes, scores, idx and cnt offsets) of a shape; a function of
+    the shape alone."""
+    d = Dims(batch, hq, hkv, seq, head_dim, causal)
+    lay = forward_layout(d, block, stride)
+    return (forward_workspace_size(d, block, stride), lay["scores"], lay["idx"], lay["cnt"])
+
+
+def _plan_of(d: Dims, block, stride):
+    return _forward_plan(d.batch, d.hq, d.hkv, d.seq, d.head_dim, d.causal, block, stride)
 
 
 def _qk_dims(q, k, causal):
@@ -299,8 +313,11 @@ def xattn_select(scores, dims: Dims, tau: float, block=BLOCK, idx=None, cnt=None
 
 def _per_head(values, dims, dtype):
     """Host array of dims.hq values (a scalar is repeated for every head)."""
-    a = np.ascontiguousarray(np.broadcast_to(np.asarray(values, dtype=dtype), (dims.hq,)))
-    return a, a.ctypes.data_as(ctypes.c_void_p)
+    a = np.asarray(values, dtype=dtype)
+    if a.shape != (dims.hq,):
+        a = np.broadcast_to(a, (dims.hq,))
+    a = np.ascontiguousarray(a)
+    return a, a.ctypes.data
 
 
 def xattn_select_heads(scores, dims: Dims, tau_h, block=BLOCK, idx=None, cnt=None,
@@ -367,15 +384,19 @@ def xattn_dense_attn(q, k, v, causal=True, o=None, lse=None, want_lse=True, stre
 
 
 def _forward_views(workspace, d, block, stride):
-    lay = forward_layout(d, block, stride)
-    nb = d.seq // block
+    """scores, idx and cnt in the workspace. One typed alias of each kind, then
+    one strided view of it per array: a slice and two views per array cost
+    about 10 us more of host time per call."""
+    _, o_scores, o_idx, o_cnt = _plan_of(d, block, stride)
+    heads, nb = d.heads, d.seq // block
+    f = workspace[:o_cnt + heads * nb * 4].view(torch.float32)
+    i = f.view(torch.int32)
+    at = f.storage_offset()
+    square, rows = (heads, nb, nb), (nb * nb, nb, 1)
     return {
-        "scores": workspace[lay["scores"]:lay["scores"] + d.heads * nb * nb * 4]
-        .view(torch.float32).view(d.heads, nb, nb),
-        "idx": workspace[lay["idx"]:lay["idx"] + d.heads * nb * nb * 4]
-        .view(torch.int32).view(d.heads, nb, nb),
-        "cnt": workspace[lay["cnt"]:lay["cnt"] + d.heads * nb * 4]
-        .view(torch.int32).view(d.heads, nb),
+        "scores": f.as_strided(square, rows, at + o_scores // 4),
+        "idx": i.as_strided(square, rows, at + o_idx // 4),
+        "cnt": i.as_strided((heads, nb), (nb, 1), at + o_cnt // 4),
     }
 
 
@@ -387,7 +408,7 @@ def xattn_forward(q, k, v, causal=True, block=BLOCK, stride=8, tau=0.9, o=None, 
     _check_workspace(workspace)
     _on_device(q=q, k=k, v=v, o=o, lse=lse, workspace=workspace)
     o, lse = _attn_outputs(q, d, o, lse, want_lse)
-    workspace = _workspace(workspace, forward_workspace_size(d, block, stride), q.device)
+    workspace = _workspace(workspace, _plan_of(d, block, stride)[0], q.device)
     _check(lib().xattn_forward(_ptr(q), _ptr(k), _ptr(v), ctypes.byref(d), block, stride,
                                float(tau), _ptr(o), _ptr(lse), _ptr(workspace),
                                workspace.numel(), _stream(stream)))
@@ -420,7 +441,7 @@ def xattn_forward_scheduled(q, k, v, step, warmup_steps=5, causal=False, block=B
     _on_device(q=q, k=k, v=v, o=o, lse=lse, workspace=workspace)
     o, lse = _attn_outputs(q, d, o, lse, want_lse)
     if workspace is not None or step >= warmup_steps:
-        workspace = _workspace(workspace, forward_workspace_size(d, block, stride), q.device)
+        workspace = _workspace(workspace, _plan_of(d, block, stride)[0], q.device)
     _check(lib().xattn_forward_scheduled(_ptr(q), _ptr(k), _ptr(v), ctypes.byref(d), block,
                                          stride, float(tau), int(step), int(warmup_steps),
                                          _ptr(o), _ptr(lse), _ptr(workspace),

@@ -79,6 +79,12 @@ struct SubRowPairing {
 };
 hipError_t launch_score(const void* q, const void* k, const XattnShape& s, int stride,
                         const int32_t* qsub, float* scores, void* scratch, hipStream_t st);
+// launch_score and launch_select with one threshold in two launches instead
+// of three, for the shapes that score_select_fits.
+bool score_select_fits(const XattnShape& s, float tau);
+hipError_t launch_score_select(const void* q, const void* k, const XattnShape& s, int stride,
+                               float tau, float* scores, int32_t* idx, int32_t* cnt, void* scratch,
+                               hipStream_t st);
 size_t score_scratch_bytes(const XattnShape& s, int stride);
 // Views of the scoring scratch: partial block masses and row statistics.
 struct ScoreScratch {

@@ -70,3 +70,23 @@ def test_hard_rows(NB, causal):
         check(X.xattn_select_topk(sc, dims, k), oracle.select_topk_rows(clean, rb, k, causal), k)
     check(X.xattn_select_ratio(sc, dims, 0.37),
           oracle.select_ratio_rows(clean, rb, 0.37, causal), "ratio")
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("hq,NB,tau", [(1, 1, 0.9), (1, 64, 0.9), (2, 65, 0.5), (3, 129, 0.95),
+                                       (8, 256, 0.9), (16, 128, 0.9), (17, 128, 0.9), (1, 257, 0.9),
+                                       (2, 33, 1.0)])
+def test_forward_lists_are_the_selection_of_its_scores(hq, NB, tau, causal):
+    """Rows few enough to be selected where they are finalised, and one past that."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(NB)
+    q, k, v = (torch.randn((n, NB * 128, 128), generator=g, device="cuda").bfloat16() * 2
+               for n in (hq, 1, 1))
+    print(f"forward lists hq={hq} NB={NB} tau={tau} causal={causal}", flush=True)
+    _, _, views = X.xattn_forward(q, k, v, causal=causal, stride=16, tau=tau)
+    sc = X.xattn_score(q, k, causal=causal, stride=16)
+    idx, cnt = X.xattn_select(sc, X.make_dims(q, k, causal), tau)
+    torch.cuda.synchronize()
+    assert torch.equal(views["scores"], sc) and torch.equal(views["cnt"], cnt)
+    kept = torch.arange(NB, device="cuda") < cnt[..., None]
+    assert torch.equal(views["idx"][kept], idx[kept])

@@ -9,7 +9,7 @@
 // with the S sub-rows reversed: no data is moved to build either.
 //
 // Kernel score_partials computes X^T = K~ Q~^T in 256 x 256 tiles on bf16
-// MFMA (fp32 accumulate; 8 waves of 128 columns x 64 rows; 64-deep K chunks
+// MFMA (16x16x32, fp32 accumulate; 8 waves of 128 columns x 64 rows; 64-deep K chunks
 // streamed by direct-to-LDS loads through a two-stage pipeline) and, in its
 // epilogue, per reduced row R and 128-column sub-tile t: the sub-tile max m
 // (log2 domain), l = sum exp2(x - m), and per key block j the partial mass
@@ -64,6 +64,36 @@ __device__ __forceinline__ float half_pair_sum(float a, float b) {
   return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
 }
 
+// The same between the 16-lane rows of a half: rows 0 and 2 return a summed
+// over their half's two rows, rows 1 and 3 return b.
+__device__ __forceinline__ float row_pair_sum(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a),
+                                                  __builtin_bit_cast(uint32_t, b), false, false);
+  return __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+}
+// The lane's number, computed where it is called for: what depends on it would
+// otherwise be kept over the main loop, in scratch memory, and each reload
+// waits for every load and store in flight.
+__device__ __forceinline__ int lane_anew() {
+  uint32_t zero = 0;
+  asm volatile("" : "+v"(zero));
+  return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+// Sum of x over lanes l, l ^ 16, l ^ 32, l ^ 48, in each of them.
+__device__ __forceinline__ float quad_sum(float x) {
+  const float z = half_pair_sum(x, x);
+  return row_pair_sum(z, z);
+}
+__device__ __forceinline__ float quad_max(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x),
+                                            __builtin_bit_cast(uint32_t, x), false, false);
+  x = fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
+  r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x),
+                                       __builtin_bit_cast(uint32_t, x), false, false);
+  return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]),
+               __builtin_bit_cast(float, (uint32_t)r[1]));
+}
+
 // NRB = reduced rows (and columns) per 128-token block = 128 / S.
 template <int NRB, bool CAUSAL>
 __global__ __launch_bounds__(kThreads, 1) void score_partials(
@@ -78,7 +108,7 @@ __global__ __launch_bounds__(kThreads, 1) void score_partials(
   // offset reaches, so they share address registers
   __shared__ __attribute__((aligned(1024))) uint16_t lds[NSTAGE * 2 * kStage];
 
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wv & 1, wr = wv >> 1;
 
@@ -122,10 +152,11 @@ __global__ __launch_bounds__(kThreads, 1) void score_partials(
     // direct-to-LDS staging: per stage each wave loads rows 32 wv .. +32 of
     // both operands, kDmaPerOp instructions (kDmaRows rows x 2 KC bytes)
     // each; rows beyond NR are clamped to NR - 1 (results masked / not stored)
+    const int ln = lane_anew();
 #pragma unroll
     for (int i = 0; i < kDmaPerOp; ++i) {
-      const int r = 32 * wv + kDmaRows * i + lane / kCPR;
-      const int c = (lane & (kCPR - 1)) ^ swz_row(r);
+      const int r = 32 * wv + kDmaRows * i + ln / kCPR;
+      const int c = (ln & (kCPR - 1)) ^ swz_row(r);
       const int ra = min(tc0 + r, NR - 1), rb = min(tR0 + r, NR - 1);
       offA[i] = (uint32_t)(((size_t)ra * KD + c * 8) * 2);
       offB[i] = (uint32_t)(((size_t)rb * S * kHeadDim + c * 8) * 2);
@@ -139,207 +170,197 @@ __global__ __launch_bounds__(kThreads, 1) void score_partials(
   const int qsub_lane = pairing.q[lane < S ? lane : 0];
   // Load pair i (operand A = K~ rows, B = Q~ rows) of chunk ch of tile t into
   // stage ch % NSTAGE.
-  auto dma_pair = [&](int ch, int i) {
+  auto dma_pair = [&](int ch, int i) __attribute__((always_inline)) {
     const int kap0 = ch * KC;
     const uint16_t* baseA = tKg + kap0;
-    const uint16_t* baseB =
-        tQh + __builtin_amdgcn_readlane(qsub_lane, kap0 / kHeadDim) * kHeadDim + kap0 % kHeadDim;
+    const uint16_t* baseB =  // a stride of 1 has one sub-row
+        tQh + (S == 1 ? 0 : __builtin_amdgcn_readlane(qsub_lane, kap0 / kHeadDim) * kHeadDim) +
+        kap0 % kHeadDim;
     const uint32_t st = lds0 + (uint32_t)((ch % NSTAGE) * kStage * 2);
     const uint32_t row_lds = (uint32_t)((32 * wv + kDmaRows * i) * KC * 2);
     dma16(baseA, offA[i], st + row_lds);
     dma16(baseB, offB[i], st + NSTAGE * kStage * 2 + row_lds);
   };
 
-  f32x16 acc[4][2];
+  // 16 x 16 tiles: acc[t][n] holds columns 16 t + 4 lg + [0, 4) of row 16 n + l16
+  f32x4 acc[8][4];
 
-  // Operands of one 16-deep k-step: 4 K~ fragments (32 columns each), 2 Q~
-  // fragments (32 rows each). Two sets alternate: while the 8 MFMAs of a
-  // k-step run from one, the next k-step's 6 reads fill the other.
-  struct Frag {
-    u32x4 a[4], b[2];
-  };
-  Frag f0, f1;
+  // Operand fragments of one 32-deep k-step: 8 of K~ (16 columns each), 4 of
+  // Q~ (16 rows each); the K~ fragment of a slot is replaced as soon as its
+  // four MFMAs have been issued, the Q~ fragments alternate between two sets.
+  u32x4 fa[8], fb[2][4];
   // Diagonal tiles are computed in full (their masked half is ~2% of the MFMA
   // work of a causal layer); a per-MFMA skip would break the inner loop into
   // branches that serialise every LDS read with its MFMA.
-  const uint32_t xa = (uint32_t)swz_row(lr);  // swizzle of this lane's rows (32 t, 64 wr: same)
-  auto read_step = [&](int stage, int ks, Frag& f) __attribute__((always_inline)) {
-    const uint16_t* A = lds + stage * kStage;
-    const uint16_t* Bm = A + NSTAGE * kStage;
-    const uint32_t coff = (uint32_t)((((2 * ks + lh) ^ xa)) << 3);  // elements
+  // LDS byte addresses of this lane's fragments, per k-step; stage, column and
+  // row tile are constant offsets. The empty asm keeps the compiler from
+  // splitting them into one address register per offset.
+  const uint32_t xa = (uint32_t)swz_row(l16);  // swizzle of this lane's rows (multiples of 16 away)
+  uint32_t ad_a[2], ad_b[2];
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
-      f.b[n] = *(const u32x4*)(Bm + (64 * wr + 32 * n + lr) * KC + coff);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-      f.a[t] = *(const u32x4*)(A + (128 * wc + 32 * t + lr) * KC + coff);
+  for (int ks = 0; ks < 2; ++ks) {
+    const uint32_t coff = ((4 * ks + lg) ^ xa) * 16;
+    ad_a[ks] = lds0 + (128 * wc + l16) * (KC * 2) + coff;
+    ad_b[ks] = lds0 + NSTAGE * kStage * 2 + (64 * wr + l16) * (KC * 2) + coff;
+    asm volatile("" : "+v"(ad_a[ks]), "+v"(ad_b[ks]));
+  }
+  typedef const __attribute__((address_space(3))) u32x4* lds_frag;
+  auto read_a = [&](int stage, int ks, int t) __attribute__((always_inline)) {
+    fa[t] = *(lds_frag)(uintptr_t)(ad_a[ks] + (uint32_t)(stage * kStage * 2 + 16 * t * KC * 2));
   };
-  auto mfma_step = [&](const Frag& f, bool zero) __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int n = 0; n < 2; ++n)
-        acc[t][n] = mfma32(as_bf16x8(f.a[t]), as_bf16x8(f.b[n]), zero ? f32x16{} : acc[t][n]);
+  auto read_b = [&](int stage, int ks, int n) __attribute__((always_inline)) {
+    fb[ks][n] = *(lds_frag)(uintptr_t)(ad_b[ks] + (uint32_t)(stage * kStage * 2 + 16 * n * KC * 2));
   };
-  // issue order of one k-step: the next k-step's 6 reads between its 8 MFMAs
-  auto step_order = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-  };
-  // One chunk, already in LDS stage STAGE with its k-step 0 in f0. Before the
-  // last k-step's MFMAs (whose operands are in registers by then) the wave
-  // waits for its loads of the next chunk and the barrier makes everyone's
-  // visible and ends all reads of this stage; the next chunk's k-step 0 is
-  // then read under the last k-step's MFMAs, so no wave starts a chunk
-  // without operands. early() and late() issue the second half of the next
-  // chunk's loads and the first half of those of the chunk after it.
-  // Against waiting at the chunk's start (both waves of a SIMD then read 6 KB
-  // before their first MFMA): 4.10 -> 4.03 ms at 128K tokens, 32/8 heads,
-  // S = 16, and 4.76 -> 4.61 ms at 64K, S = 4 (finalize included). The rest
-  // is the power limit: MFMA pipes 68 % busy at 1.50 GHz, where a library GEMM
-  // of 16384^3 keeps them 90 % busy at 1.55 GHz.
-  auto chunk = [&](auto stage_tag, bool zero, auto early, auto late) __attribute__((always_inline)) {
+  // One chunk, already in LDS stage STAGE with its k-step 0 in fa, fb[0]: 16
+  // steps of 4 MFMAs (one K~ fragment against the four Q~ ones). Steps 0-7
+  // read k-step 1. Two steps later, when those reads are in registers, the
+  // wave waits for its loads of the next chunk; the barrier makes everyone's
+  // visible and ends all reads of this stage. The remaining steps read the
+  // next chunk's k-step 0 and issue the loads of the chunk after it (load(i),
+  // i < 4), so no wave starts a chunk without operands.
+  // 16x16x32 MFMAs, not 32x32x16: with the accumulators in VGPRs and operands
+  // that change, the latter sustain 1.65 PFLOP/s on zeros and 1.29 on normal
+  // data (2 waves per SIMD, no memory traffic), these 2.45 and 2.05; at the
+  // power limit the shader clock rises from 1.45 to 1.62 GHz. xattn_score with
+  // waits at the chunk's start and 32x32x16, with these waits, with both
+  // (finalize included): 128K, 32/8 heads, S = 16: 4.05, 3.99, 3.72 ms; 64K,
+  // S = 4: 4.71, 4.36, 4.10 ms; 32K, S = 8: 0.571, 0.548, 0.514 ms.
+  auto chunk = [&](auto stage_tag, bool zero, bool read_next, auto load) __attribute__((always_inline)) {
     constexpr int STAGE = decltype(stage_tag)::value;
-    early();
-    read_step(STAGE, 1, f1);
-    mfma_step(f0, zero);
-    step_order();
-    __builtin_amdgcn_sched_barrier(0);
-    read_step(STAGE, 2, f0);
-    mfma_step(f1, false);
-    step_order();
-    __builtin_amdgcn_sched_barrier(0);
-    read_step(STAGE, 3, f1);
-    mfma_step(f0, false);
-    step_order();
-    __builtin_amdgcn_sched_barrier(0);
-    wait_vmcnt<0>();
-    barrier_nofence();
-    late();
-    read_step(STAGE ^ 1, 0, f0);
-    mfma_step(f1, false);
-    step_order();
-    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      const int t = s & 7, ks = s >> 3;
+      if (s == 10) {
+        wait_vmcnt<0>();
+        barrier_nofence();
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        // back and forth, so that one operand stays the same (0.7 % faster)
+        const int n = s & 1 ? 3 - i : i;
+        acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            as_bf16x8(fa[t]), as_bf16x8(fb[ks][n]), zero && ks == 0 ? f32x4{} : acc[t][n], 0, 0, 0);
+      }
+      if (s < 8) {
+        read_a(STAGE, 1, t);
+        if (s >= 4) read_b(STAGE, 1, s - 4);
+      }
+      if (s >= 10) {  // the next chunk's k-step 0: Q~ and the first K~ fragments first
+        constexpr int N = STAGE ^ 1;
+        if (read_next) {
+          if (s == 10) { read_a(N, 0, 0); read_b(N, 0, 0); }
+          if (s == 11) { read_b(N, 0, 1); read_b(N, 0, 2); }
+          if (s == 12) { read_b(N, 0, 3); read_a(N, 0, 1); }
+          if (s == 13) { read_a(N, 0, 2); read_a(N, 0, 3); }
+          if (s == 14) { read_a(N, 0, 4); read_a(N, 0, 5); }
+          if (s == 15) { read_a(N, 0, 6); read_a(N, 0, 7); }
+        }
+        if (s == 15 || s % 2 == 0) load(s == 15 ? 3 : (s - 10) / 2);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
-  static_assert(KC == 64 && kDmaPerOp == 4 && NSTAGE == 2, "the chunk's four k-steps");
+  static_assert(KC == 64 && kDmaPerOp == 4 && NSTAGE == 2, "the chunk's two k-steps, four loads");
 
-  auto epilogue = [&](const int h, const int R0, const int c0) {
-    // ---- epilogue per 32-row slab n: this lane owns reduced row R and 64 of the
-    // wave's 128 columns; lane (lr, 1-lh) owns the other 64.
+  auto epilogue = [&](const int h, const int R0, const int c0) __attribute__((always_inline)) {
+    // ---- epilogue per 16-row slab n: this lane owns row R and 32 of the wave's
+    // 128 columns; the lanes 16, 32 and 48 away own the others.
     const int csub = c0 + 128 * wc;  // first column of this wave's sub-tile
     const int tsub_idx = csub / TSUB;
     const int j0 = csub / NRB;
-  #pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      const int R = R0 + 64 * wr + 32 * n + lr;
+    const int ln = lane_anew(), l16 = ln & 15, lg = ln >> 4;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int Rslab = R0 + 64 * wr + 16 * n;
+      const int R = Rslab + l16;
       // Invalid columns (c > R when causal, c >= NR) occur only in sub-tiles
       // that reach past the slab's first row or the reduced length; the empty
       // asm keeps this uniform branch from becoming selects on every tile.
-      const int Rslab = R0 + 64 * wr + 32 * n;
       if ((CAUSAL && csub + 127 > Rslab) || csub + 127 >= NR) {
         asm volatile("");
         // last valid column of this row, relative to the lane's first one
-        const int last = (CAUSAL ? min(R, NR - 1) : NR - 1) - csub - 4 * lh;
-  #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-  #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (32 * t + 8 * (r >> 2) + (r & 3) > last) acc[t][n][r] = -INFINITY;
+        const int last = (CAUSAL ? min(R, NR - 1) : NR - 1) - csub - 4 * lg;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (16 * t + e > last) acc[t][n][e] = -INFINITY;
         }
       }
       // max of the raw products (the scale is positive), then every term as
       // one fma inside the exponential: p = 2^(x scale - m)
       float mloc = -INFINITY;
-  #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-  #pragma unroll
-        for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, acc[t][n][r]);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mloc = fmaxf(mloc, acc[t][n][e]);
       }
-      const float m = fmaxf(mloc, __shfl_xor(mloc, 32)) * scale_log2;
+      const float m = quad_max(mloc) * scale_log2;
       const float mref = (m == -INFINITY) ? 0.f : m;
-      float gsum[16];  // groups of 4 consecutive columns: group gi = 4 t + r / 4
+      float gsum[8];  // this lane's 4 columns of tile t
       float lloc = 0.f;
-  #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-  #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          float sum = 0.f;
-  #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float p = fast_exp2(fmaf(acc[t][n][4 * g4 + e], scale_log2, -mref));
-            acc[t][n][4 * g4 + e] = p;
-            sum += p;
-          }
-          gsum[4 * t + g4] = sum;
-          lloc += sum;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        float sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float p = fast_exp2(fmaf(acc[t][n][e], scale_log2, -mref));
+          if constexpr (NRB == 2) acc[t][n][e] = p;
+          sum += p;
         }
+        gsum[t] = sum;
+        lloc += sum;
       }
-      const float l = lloc + __shfl_xor(lloc, 32);
+      const float l = quad_sum(lloc);
       const bool rvalid = R < NR;
       // part is [head][query block][key block][row in block] (causal: key
       // blocks <= the query block only, rows packed as a triangle): what the
-      // finalize workgroup of one query block reads is one contiguous slab;
-      // a half-wave writes 32 / NRB runs of NRB consecutive floats per block.
+      // finalize workgroup of one query block reads is one contiguous slab.
       const int Rv = rvalid ? R : 0;
       const int qb = Rv / NRB;
       float* pcol = part + part_row(h, qb, NB, CAUSAL) * NRB + (Rv % NRB);
       // key block j of this row is stored if it exists and, when causal, is
       // not above the diagonal (those are fully masked and have no slot)
-      auto keep = [&](int j) { return rvalid && j < NB && (!CAUSAL || j <= qb); };
-  
-      if constexpr (NRB >= 8) {
-        // group gi covers columns 8 gi + 4 lh + [0, 4): local block gi / (NRB / 8)
-        constexpr int GPB = NRB / 8;
-        constexpr int NBL = TSUB / NRB;
-        auto block_sum = [&](int jb) {
-          float sum = 0.f;
-  #pragma unroll
-          for (int x = 0; x < GPB; ++x) sum += gsum[jb * GPB + x];
-          return sum;
-        };
-        if constexpr (NBL >= 2) {
-          // blocks x and NBL/2 + x in one exchange: lanes < 32 end up with
-          // block x's total over both column halves, lanes >= 32 with block
-          // NBL/2 + x's, each the one it stores
-  #pragma unroll
-          for (int x = 0; x < NBL / 2; ++x) {
-            const float tot = half_pair_sum(block_sum(x), block_sum(NBL / 2 + x));
-            const int jb = lh * (NBL / 2) + x;
-            if (keep(j0 + jb)) pcol[(size_t)(j0 + jb) * NRB] = tot;
-          }
-        } else {
-          const float s0 = block_sum(0);
-          const float tot = half_pair_sum(s0, s0);
-          if (lh == 0 && keep(j0)) pcol[(size_t)j0 * NRB] = tot;
-        }
-      } else if constexpr (NRB == 4) {
-        // each group of 4 columns is one block: local block 2 gi + lh
-  #pragma unroll
-        for (int gi = 0; gi < 16; ++gi) {
-          const int j = j0 + 2 * gi + lh;
-          if (keep(j)) pcol[(size_t)j * NRB] = gsum[gi];
-        }
-      } else {  // NRB == 2: each group holds two blocks
+      auto put = [&](int j, float v) {
+        if (rvalid && j < NB && (!CAUSAL || j <= qb)) pcol[(size_t)j * NRB] = v;
+      };
+      // A lane ends up with the totals that it stores: of four values summed
+      // over the four lanes, lane group lg takes the lg-th.
+      auto quad_of = [&](float v0, float v1, float v2, float v3) {
+        return row_pair_sum(half_pair_sum(v0, v2), half_pair_sum(v1, v3));
+      };
+      if constexpr (NRB == 128) {
+        if (lg == 0) put(j0, l);
+      } else if constexpr (NRB == 64) {
+        const float z = half_pair_sum(gsum[0] + gsum[1] + gsum[2] + gsum[3],
+                                      gsum[4] + gsum[5] + gsum[6] + gsum[7]);
+        const float tot = row_pair_sum(z, z);
+        if ((lg & 1) == 0) put(j0 + (lg >> 1), tot);
+      } else if constexpr (NRB == 32) {
+        put(j0 + lg, quad_of(gsum[0] + gsum[1], gsum[2] + gsum[3], gsum[4] + gsum[5],
+                             gsum[6] + gsum[7]));
+      } else if constexpr (NRB == 16) {
+#pragma unroll
+        for (int u = 0; u < 8; u += 4)
+          put(j0 + u + lg, quad_of(gsum[u], gsum[u + 1], gsum[u + 2], gsum[u + 3]));
+      } else if constexpr (NRB == 8) {  // a tile's columns 0-7 are lane groups 0 and 1
+#pragma unroll
+        for (int t = 0; t < 8; t += 2)
+          put(j0 + 2 * (t + (lg & 1)) + (lg >> 1), row_pair_sum(gsum[t], gsum[t + 1]));
+      } else if constexpr (NRB == 4) {  // this lane's 4 columns of a tile are one block
+#pragma unroll
+        for (int t = 0; t < 8; ++t) put(j0 + 4 * t + lg, gsum[t]);
+      } else {  // NRB == 2: they are two
         static_assert(NRB == 2, "stride must divide the block");
-  #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-  #pragma unroll
-          for (int g4 = 0; g4 < 4; ++g4) {
-            const int gi = 4 * t + g4;
-            const int j = j0 + 4 * gi + 2 * lh;
-            if (keep(j)) pcol[(size_t)j * NRB] = acc[t][n][4 * g4] + acc[t][n][4 * g4 + 1];
-            if (keep(j + 1))
-              pcol[(size_t)(j + 1) * NRB] = acc[t][n][4 * g4 + 2] + acc[t][n][4 * g4 + 3];
-          }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          put(j0 + 8 * t + 2 * lg, acc[t][n][0] + acc[t][n][1]);
+          put(j0 + 8 * t + 2 * lg + 1, acc[t][n][2] + acc[t][n][3]);
         }
       }
       // causal: a sub-tile starting after the row has no stats slot (all its
       // columns are masked for that row)
-      if (rvalid && lh == 0 && tsub_idx < NT && (!CAUSAL || R >= tsub_idx * TSUB))
+      if (rvalid && lg == 0 && tsub_idx < NT && (!CAUSAL || R >= tsub_idx * TSUB))
         stats[stats_at(h, tsub_idx, R, NR, NT, CAUSAL)] = make_float2(m, l);
     }
   };
@@ -348,37 +369,45 @@ __global__ __launch_bounds__(kThreads, 1) void score_partials(
   load_tile(lo + k8);
 #pragma unroll
   for (int i = 0; i < kDmaPerOp; ++i) dma_pair(0, i);
-  dma_pair(1, 0);
-  dma_pair(1, 1);
-  wait_vmcnt<4>();  // chunk 0 has landed
+#pragma unroll
+  for (int i = 0; i < kDmaPerOp; ++i) dma_pair(1, i);
+  wait_vmcnt<2 * kDmaPerOp>();  // chunk 0 has landed
   barrier_nofence();
-  read_step(0, 0, f0);
+  // k-step 0 of a tile (not before the epilogue: its registers are needed there)
+  auto read_first = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) read_b(0, 0, n);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) read_a(0, 0, t);
+  };
+  read_first();
   using Even = std::integral_constant<int, 0>;
   using Odd = std::integral_constant<int, 1>;
   for (int it = k8; it < cnt_x; it += nper) {
     // Chunks in pairs (stage 0, stage 1). The last pair switches to the next
-    // tile between its chunks: that tile's chunk 0 and half of its chunk 1
-    // are then loaded before the epilogue. After the last tile the same
-    // tile's chunks are loaded again (in bounds, never used).
+    // tile before it issues its first loads: that tile's chunks 0 and 1 are
+    // then loaded before the epilogue. After the last tile the same tile's
+    // chunks are loaded again (in bounds, never used).
     const int h_done = th, R0_done = tR0, c0_done = tc0;
     auto pair = [&](int ch, bool zero) __attribute__((always_inline)) {
-      chunk(Even{}, zero, [&] { dma_pair(ch + 1, 2); dma_pair(ch + 1, 3); },
-            [&] { dma_pair(ch + 2, 0); dma_pair(ch + 2, 1); });
-      chunk(Odd{}, false, [&] { dma_pair(ch + 2, 2); dma_pair(ch + 2, 3); },
-            [&] { dma_pair(ch + 3, 0); dma_pair(ch + 3, 1); });
+      chunk(Even{}, zero, true, [&](int i) { dma_pair(ch + 2, i); });
+      chunk(Odd{}, false, true, [&](int i) { dma_pair(ch + 3, i); });
     };
-    if constexpr (NCH > 2) pair(0, true);
+    if constexpr (NCH == 4) {  // (a loop of one pass: as straight code it spills)
+      int once = 1;
+      asm volatile("" : "+s"(once));
+#pragma unroll 1
+      for (int i = 0; i < once; ++i) pair(0, true);
+    } else if constexpr (NCH > 2) {
+      pair(0, true);
+    }
 #pragma unroll 1
     for (int ch = 2; ch + 2 < NCH; ch += 2) pair(ch, false);
-    chunk(Even{}, NCH == 2, [&] { dma_pair(NCH - 1, 2); dma_pair(NCH - 1, 3); },
-          [&] {
-            if (it + nper < cnt_x) load_tile(lo + it + nper);
-            dma_pair(0, 0);
-            dma_pair(0, 1);
-          });
-    chunk(Odd{}, false, [&] { dma_pair(0, 2); dma_pair(0, 3); },
-          [&] { dma_pair(1, 0); dma_pair(1, 1); });
+    if (it + nper < cnt_x) load_tile(lo + it + nper);
+    chunk(Even{}, NCH == 2, true, [&](int i) { dma_pair(0, i); });
+    chunk(Odd{}, false, false, [&](int i) { dma_pair(1, i); });
     epilogue(h_done, R0_done, c0_done);
+    read_first();
   }
   wait_vmcnt<0>();  // the last loads land before the LDS is released
 }

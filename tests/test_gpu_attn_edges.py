@@ -84,3 +84,24 @@ def test_malformed_lists_stay_in_bounds(hq, NB):
     o, _ = X.xattn_block_sparse_attn(q, k, v, idx, cnt, causal=False)
     torch.cuda.synchronize()
     assert torch.isfinite(o.float()).all() and (o[:, :128] == 0).all()
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("hq,NB", [(1, 1), (2, 5), (1, 50)])
+def test_products_that_overflow(hq, NB, causal):
+    """A query whose products with one wave's first keys are -inf gives them no weight."""
+    L = 128 * NB
+    x = W.generate(W.small("edge", L, hq=hq, hkv=1, seed=660))
+    big = int(np.float32(3e38).view(np.uint32) >> 16)
+    q, k = x["q"].copy(), x["k"].copy()
+    q[..., 0] = 0
+    k[..., 0] = 0
+    q[..., 40::61, 0] = big
+    k[..., :32, 0] = big | 0x8000
+    print(f"attn overflow hq={hq} NB={NB} causal={causal}", flush=True)
+    o, lse = X.xattn_dense_attn(dev_bf16(q), dev_bf16(k), dev_bf16(x["v"]), causal=causal)
+    torch.cuda.synchronize()
+    o_ref, lse_ref = oracle.dense_attn_rows(q, k, x["v"], 128, causal)
+    e = np.abs(host_f32(o).reshape(o_ref.shape).astype(np.float64) - o_ref)
+    assert e.max() <= OUT_MAX_ABS and e.mean() <= OUT_MEAN_ABS
+    np.testing.assert_allclose(host_f32(lse).reshape(lse_ref.shape), lse_ref, rtol=2e-3, atol=2e-2)

@@ -515,11 +515,9 @@ __global__ __launch_bounds__(kSmallThreads) void attn_small_kernel(
   // K(i + 1) and V(i) are in registers; K(i + 2) and V(i + 1) are loaded in their place.
   auto step = [&](int i, f32x16& sc, f32x16& sn) __attribute__((always_inline)) {
     const int key2 = key_at(i + 2);
-    const bool past = i >= n_steps;  // the second step of an odd last pair
-    if ((CAUSAL && key0 + kKeysW - 1 > q0) || past) {
+    if (CAUSAL && key0 + kKeysW - 1 > q0) {
       asm volatile("");
-      // last visible key, relative to the lane's first one
-      const int last = past ? -1 : qi - key0 - 4 * lh;
+      const int last = qi - key0 - 4 * lh;  // last visible key, relative to the lane's first one
 #pragma unroll
       for (int r = 0; r < 16; ++r)
         if (8 * (r >> 2) + (r & 3) > last) sc[r] = -INFINITY;
@@ -585,7 +583,9 @@ __global__ __launch_bounds__(kSmallThreads) void attn_small_kernel(
     __builtin_amdgcn_sched_barrier(0);
     for (int i = 0; i < n_steps; i += 2) {
       step(i, sa, sb);
-      step(i + 1, sb, sa);
+      // No step past the end of an odd number: the zero weights of its keys
+      // would turn an infinite value of theirs into NaN.
+      if (i + 1 < n_steps) step(i + 1, sb, sa);
     }
   }
 

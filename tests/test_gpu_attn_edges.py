@@ -105,3 +105,35 @@ def test_products_that_overflow(hq, NB, causal):
     e = np.abs(host_f32(o).reshape(o_ref.shape).astype(np.float64) - o_ref)
     assert e.max() <= OUT_MAX_ABS and e.mean() <= OUT_MEAN_ABS
     np.testing.assert_allclose(host_f32(lse).reshape(lse_ref.shape), lse_ref, rtol=2e-3, atol=2e-2)
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("hq,hkv,NB", [(1, 1, 1), (1, 1, 2), (1, 1, 7), (2, 1, 5), (1, 1, 50),
+                                       (16, 2, 9), (3, 1, 50)])
+def test_infinite_values_reach_their_queries_alone(hq, hkv, NB, causal):
+    """A value of +-inf at a visible key gives +-inf in its feature and nothing in the others,
+    on both sides of the split (the last two grids are past it) and for lists of every length."""
+    L = 128 * NB
+    x = W.generate(W.small("edge", L, hq=hq, hkv=hkv, seed=680 + NB))
+    # inputs a tenth as large: every visible key keeps a weight above 0
+    q, k = (W.to_bf16_bits(0.1 * W.bf16_bits_to_f32(x[n])) for n in "qk")
+    v, zero = x["v"].copy(), x["v"].copy()
+    inf = int(np.float32(np.inf).view(np.uint32) >> 16)
+    v[:, ::128, 5], v[:, ::128, 77] = inf, inf | 0x8000  # the first key of a block: all see it
+    zero[:, ::128, 5] = zero[:, ::128, 77] = 0
+    idx, cnt = _lists(hq, NB, causal, np.random.default_rng(NB))
+    full = np.tile(np.arange(NB, dtype=np.int32), (hq * NB, 1))
+    n = np.tile(np.arange(1, NB + 1) if causal else np.full(NB, NB), hq).astype(np.int32)
+    rest = np.setdiff1d(np.arange(128), [5, 77])
+    for tag, ix, ct in (("lists", idx, cnt), ("full", full, n)):
+        print(f"attn inf hq={hq} NB={NB} causal={causal} {tag}", flush=True)
+        o, _ = X.xattn_block_sparse_attn(
+            dev_bf16(q), dev_bf16(k), dev_bf16(v), torch.from_numpy(ix.reshape(hq, NB, NB)).cuda(),
+            torch.from_numpy(ct.reshape(hq, NB)).cuda(), causal=causal)
+        torch.cuda.synchronize()
+        o_ref, _ = oracle.sparse_attn_rows(q, k, zero, 128, ix, ct, causal)
+        og = host_f32(o).reshape(o_ref.shape)
+        some = ct > 0
+        assert np.all(np.isposinf(og[some][..., 5])) and np.all(np.isneginf(og[some][..., 77]))
+        e = np.abs(og[..., rest].astype(np.float64) - o_ref[..., rest])
+        assert e.max() <= OUT_MAX_ABS and e.mean() <= OUT_MEAN_ABS

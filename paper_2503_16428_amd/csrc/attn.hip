@@ -271,7 +271,9 @@ __device__ __forceinline__ void attn_body(
     // whenever no lane needs them.
     if (__ballot(mt > m_ref + kRescaleSlack) != 0) {
       const float m_new = fmaxf(m_ref, mt);
-      const float alpha = fast_exp2(m_ref - m_new);  // m_ref = -inf -> 0
+      // 0 where m_ref is -inf, also for a query whose scores so far are all
+      // -inf (products that overflow) when another one moves its reference
+      const float alpha = m_new == -INFINITY ? 0.f : fast_exp2(m_ref - m_new);
       m_ref = m_new;
       l_run *= alpha;
 #pragma unroll
@@ -528,8 +530,6 @@ __global__ __launch_bounds__(kSmallThreads) void attn_small_kernel(
     const float mt = half_max(mraw) * scale_log2;
     if (__ballot(mt > m_ref + kRescaleSlack) != 0) {  // lazy rescaling, as in attn_body
       const float m_new = fmaxf(m_ref, mt);
-      // 0 also for a query whose scores so far are all -inf (products that
-      // overflow): a wave may hold no other keys of its row
       const float alpha = m_new == -INFINITY ? 0.f : fast_exp2(m_ref - m_new);
       m_ref = m_new;
       l_run *= alpha;

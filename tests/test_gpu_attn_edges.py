@@ -137,3 +137,27 @@ def test_infinite_values_reach_their_queries_alone(hq, hkv, NB, causal):
         assert np.all(np.isposinf(og[some][..., 5])) and np.all(np.isneginf(og[some][..., 77]))
         e = np.abs(og[..., rest].astype(np.float64) - o_ref[..., rest])
         assert e.max() <= OUT_MAX_ABS and e.mean() <= OUT_MEAN_ABS
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("spoiled", [64, 128, 200])
+@pytest.mark.parametrize("hq,NB", [(2, 5), (1, 50), (16, 9), (3, 50)])
+def test_products_that_overflow_over_whole_tiles(hq, NB, spoiled, causal):
+    """As above with every key of the first half-tile, block or more: a query has seen only
+    -inf when another query of its wave moves its reference. The last two grids run
+    128-query workgroups."""
+    L = 128 * NB
+    x = W.generate(W.small("edge", L, hq=hq, hkv=1, seed=670))
+    big = int(np.float32(3e38).view(np.uint32) >> 16)
+    q, k = x["q"].copy(), x["k"].copy()
+    q[..., 0] = 0
+    k[..., 0] = 0
+    q[..., 261::61, 0] = big  # queries that see keys past the spoiled ones
+    k[..., :spoiled, 0] = big | 0x8000
+    print(f"attn overflow hq={hq} NB={NB} spoiled={spoiled} causal={causal}", flush=True)
+    o, lse = X.xattn_dense_attn(dev_bf16(q), dev_bf16(k), dev_bf16(x["v"]), causal=causal)
+    torch.cuda.synchronize()
+    o_ref, lse_ref = oracle.dense_attn_rows(q, k, x["v"], 128, causal)
+    e = np.abs(host_f32(o).reshape(o_ref.shape).astype(np.float64) - o_ref)
+    assert e.max() <= OUT_MAX_ABS and e.mean() <= OUT_MEAN_ABS
+    np.testing.assert_allclose(host_f32(lse).reshape(lse_ref.shape), lse_ref, rtol=2e-3, atol=2e-2)

@@ -228,7 +228,11 @@ def _forward_plan(batch, hq, hkv, seq, head_dim, causal, block, stride):
 
 
 def _plan_of(d: Dims, block, stride):
-    return _forward_plan(d.batch, d.hq, d.hkv, d.seq, d.head_dim, d.causal, block, stride)
+    # Only plain ints are keys: other integers that ctypes takes may not hash
+    # (a 0-d array) or hash by identity (a tensor, whose value may change).
+    plan = (_forward_plan if type(block) is int and type(stride) is int
+            else _forward_plan.__wrapped__)
+    return plan(d.batch, d.hq, d.hkv, d.seq, d.head_dim, d.causal, block, stride)
 
 
 def _qk_dims(q, k, causal):

@@ -1,6 +1,7 @@
 """The binding rejects every shape or dtype mismatch before any kernel is
 launched (CPU only: the tensors here live on the host, and a call that
 passed every shape check would stop at the device check instead)."""
+import numpy as np
 import pytest
 import torch
 
@@ -101,3 +102,35 @@ def test_forward_workspace_is_checked():
                                                                                 dtype=torch.uint8))
     expect("workspace must be", X.xattn_forward_scheduled, q, k, v, 7,
            workspace=torch.zeros(16, dtype=torch.int32))
+
+
+@pytest.mark.parametrize("integer", [int, np.int64, np.array, torch.tensor])
+def test_workspace_sizes_of_every_kind_of_integer(integer):
+    """Sizes follow the value of block and stride at each call, whatever holds it."""
+    d = B.Dims(1, H, HKV, L, D, 1)
+    for stride in (16, 4, 8):
+        want = B.forward_workspace_size(d, 128, stride)
+        assert B._plan_of(d, 128, integer(stride))[0] == want
+        assert B._plan_of(d, integer(128), stride)[0] == want
+
+
+def test_workspace_sizes_follow_a_changed_tensor():
+    d, s = B.Dims(1, H, HKV, L, D, 1), torch.tensor(16)
+    B._plan_of(d, 128, s)
+    s.fill_(2)
+    assert B._plan_of(d, 128, s)[0] == B.forward_workspace_size(d, 128, 2)
+
+
+@pytest.mark.parametrize("integer", [int, np.int64, np.array, torch.tensor])
+def test_forward_views_for_every_kind_of_integer(integer):
+    d = B.Dims(1, H, HKV, L, D, 1)
+    lay = B.forward_layout(d, 128, 8)
+    ws = torch.arange(B.forward_workspace_size(d, 128, 8) + 512, dtype=torch.int64).to(torch.uint8)
+    for at in (0, 256):  # a workspace inside a larger one
+        w = ws[at:]
+        v = B._forward_views(w, d, integer(128), integer(8))
+        for name, dtype, n in (("scores", torch.float32, NB), ("idx", torch.int32, NB),
+                               ("cnt", torch.int32, 1)):
+            assert v[name].shape == ((H, NB, NB) if n > 1 else (H, NB))
+            assert v[name].dtype == dtype and v[name].data_ptr() == w.data_ptr() + lay[name]
+            assert v[name].is_contiguous()

@@ -706,22 +706,22 @@ __global__ __launch_bounds__(256, 1) void score_partials_small(
 
 // One workgroup (4 waves) per (query head, query block) row: the row's
 // scores from its partial sums and tile statistics (finalize_row).
-template <bool CAUSAL>
+template <bool CAUSAL, bool MANY>
 __global__ __launch_bounds__(kFinThreads) void score_finalize(const float* __restrict__ part,
                                                               const float2* __restrict__ stats,
                                                               int NR, int NB, int NT, int nrb,
                                                               float* __restrict__ scores) {
   __shared__ FinalizeLds lds;
   const int h = blockIdx.x / NB, b = blockIdx.x % NB;
-  finalize_row<CAUSAL>(part, stats, NR, NB, NT, nrb, h, b, scores + ((size_t)h * NB + b) * NB,
-                       lds);
+  finalize_row<CAUSAL, MANY>(part, stats, NR, NB, NT, nrb, h, b,
+                             scores + ((size_t)h * NB + b) * NB, lds);
 }
 
 // The same, and the row's block list by wave 0 from the scores just written
 // (they come back out of the L1 / L2 of the compute unit that wrote them):
 // one launch and one pass less where the rows are few. NPL as in
 // select_kernel.
-template <int NPL, bool CAUSAL>
+template <int NPL, bool CAUSAL, bool MANY>
 __global__ __launch_bounds__(kFinThreads) void score_finalize_select(
     const float* __restrict__ part, const float2* __restrict__ stats, int NR, int NB, int NT,
     int nrb, float tau, float* scores, int32_t* __restrict__ idx, int32_t* __restrict__ cnt) {
@@ -729,7 +729,7 @@ __global__ __launch_bounds__(kFinThreads) void score_finalize_select(
   __shared__ uint32_t stage[64];
   const int h = blockIdx.x / NB, b = blockIdx.x % NB;
   const size_t row = (size_t)h * NB + b;
-  finalize_row<CAUSAL>(part, stats, NR, NB, NT, nrb, h, b, scores + row * NB, lds);
+  finalize_row<CAUSAL, MANY>(part, stats, NR, NB, NT, nrb, h, b, scores + row * NB, lds);
   __syncthreads();
   if (threadIdx.x >= kWave) return;
   const int m = CAUSAL ? b + 1 : NB;
@@ -852,18 +852,23 @@ static hipError_t launch_score_partials(const void* q, const void* k, const Xatt
   }
 }
 
-template <int NPL>
+template <int NPL, bool CAUSAL>
 static void launch_finalize_select(const XattnShape& s, int stride, float tau, float* scores,
                                    int32_t* idx, int32_t* cnt, const ScoreScratch& v,
                                    hipStream_t st) {
   const int NR = s.seq / stride, NB = s.NB(), NT = ceil_div(NR, TSUB), nrb = kBlock / stride;
-  if (s.causal)
-    hipLaunchKernelGGL((score_finalize_select<NPL, true>), dim3(s.HQ() * NB), dim3(kFinThreads), 0,
-                       st, v.part, (const float2*)v.stats, NR, NB, NT, nrb, tau, scores, idx, cnt);
-  else
-    hipLaunchKernelGGL((score_finalize_select<NPL, false>), dim3(s.HQ() * NB), dim3(kFinThreads),
-                       0, st, v.part, (const float2*)v.stats, NR, NB, NT, nrb, tau, scores, idx,
-                       cnt);
+  auto kernel = nrb >= kFinalizeMany ? score_finalize_select<NPL, CAUSAL, true>
+                                     : score_finalize_select<NPL, CAUSAL, false>;
+  hipLaunchKernelGGL(kernel, dim3(s.HQ() * NB), dim3(kFinThreads), 0, st, v.part,
+                     (const float2*)v.stats, NR, NB, NT, nrb, tau, scores, idx, cnt);
+}
+
+template <int NPL>
+static void launch_finalize_select_c(const XattnShape& s, int stride, float tau, float* scores,
+                                     int32_t* idx, int32_t* cnt, const ScoreScratch& v,
+                                     hipStream_t st) {
+  if (s.causal) launch_finalize_select<NPL, true>(s, stride, tau, scores, idx, cnt, v, st);
+  else launch_finalize_select<NPL, false>(s, stride, tau, scores, idx, cnt, v, st);
 }
 
 // The launch it saves is 2 us of the layer: 1K tokens, one head, 27.8 -> 26.4
@@ -880,9 +885,9 @@ hipError_t launch_score_select(const void* q, const void* k, const XattnShape& s
   hipError_t e = launch_score_partials(q, k, s, stride, nullptr, scratch, st);
   if (e != hipSuccess) return e;
   const ScoreScratch v = score_scratch_views(s, stride, scratch);
-  if (s.NB() <= 64) launch_finalize_select<1>(s, stride, tau, scores, idx, cnt, v, st);
-  else if (s.NB() <= 128) launch_finalize_select<2>(s, stride, tau, scores, idx, cnt, v, st);
-  else launch_finalize_select<4>(s, stride, tau, scores, idx, cnt, v, st);
+  if (s.NB() <= 64) launch_finalize_select_c<1>(s, stride, tau, scores, idx, cnt, v, st);
+  else if (s.NB() <= 128) launch_finalize_select_c<2>(s, stride, tau, scores, idx, cnt, v, st);
+  else launch_finalize_select_c<4>(s, stride, tau, scores, idx, cnt, v, st);
   return hipGetLastError();
 }
 
@@ -893,11 +898,10 @@ hipError_t launch_score(const void* q, const void* k, const XattnShape& s, int s
   const int NR = s.seq / stride, NB = s.NB(), NT = ceil_div(NR, TSUB);
   const int nrb = kBlock / stride;
   const ScoreScratch v = score_scratch_views(s, stride, scratch);
-  if (s.causal)
-    hipLaunchKernelGGL(score_finalize<true>, dim3(s.HQ() * NB), dim3(kFinThreads), 0, st, v.part,
-                       (const float2*)v.stats, NR, NB, NT, nrb, scores);
-  else
-    hipLaunchKernelGGL(score_finalize<false>, dim3(s.HQ() * NB), dim3(kFinThreads), 0, st,
-                       v.part, (const float2*)v.stats, NR, NB, NT, nrb, scores);
+  const bool many = nrb >= kFinalizeMany;
+  auto kernel = s.causal ? (many ? score_finalize<true, true> : score_finalize<true, false>)
+                         : (many ? score_finalize<false, true> : score_finalize<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(s.HQ() * NB), dim3(kFinThreads), 0, st, v.part,
+                     (const float2*)v.stats, NR, NB, NT, nrb, scores);
   return hipGetLastError();
 }

@@ -12,6 +12,7 @@ constexpr int kTsub = 128;      // reduced-column sub-tile owning one (max, sum)
 constexpr int kFactorMax = 4096;  // (row, sub-tile) factors staged in LDS (16 KB) at a time
 constexpr int kFinUnroll = 4;   // independent 16-byte partial-sum loads per thread
 constexpr int kFinThreads = 256;
+constexpr int kFinalizeMany = 64;  // reduced rows per block from which a thread has many sub-tiles
 
 // Partial block masses, fp32: row (h, query block b) holds nrb floats per key
 // block j, j < b + 1 when causal (the rows packed as a lower triangle), j <
@@ -61,7 +62,12 @@ struct FinalizeLds {
 // 4096 at 64K tokens, S = 1: 65536), and reading four stats and evaluating
 // four exponentials per float4 instead took 0.420 ms at 64K, 32/8 heads,
 // S = 4 (0.54 GB of partial sums). Called by all kFinThreads threads.
-template <bool CAUSAL>
+// MANY (nrb >= kFinalizeMany): a thread has up to 1024 sub-tiles, and one load
+// at a time makes the row a chain of latencies; four are in flight
+// (xattn_score, S = 1, causal: 32K tokens, 2 heads 540 -> 464 us; 4K, one head
+// 24 -> 20 us). With smaller nrb it has few, and the unrolled loops cost 0.5
+// us of 46 (8K, 32 heads, S = 16).
+template <bool CAUSAL, bool MANY>
 __device__ __forceinline__ void finalize_row(const float* __restrict__ part,
                                              const float2* __restrict__ stats, int NR, int NB,
                                              int NT, int nrb, int h, int b,
@@ -78,18 +84,27 @@ __device__ __forceinline__ void finalize_row(const float* __restrict__ part,
   // the groups of max(nrb, 64) threads
   const int group = nrb > 64 ? nrb : 64, g_own = tid / group;
   const bool writes = tid % group < nrb;
+  // f(t) for this thread's sub-tiles of t0 .. t1 - 1, in order
+  auto each = [&](int t0, int t1, auto f) {
+    if constexpr (MANY) {
+#pragma unroll 4
+      for (int t = t0 + t_own; t < t1; t += tstep) f(t);
+    } else {
+      for (int t = t0 + t_own; t < t1; t += tstep) f(t);
+    }
+  };
   float m = -INFINITY;
-  for (int t = t_own; t < tn; t += tstep) m = fmaxf(m, st(t).x);
+  each(0, tn, [&](int t) { m = fmaxf(m, st(t).x); });
   for (int off = 32; off >= nrb; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
   if (writes) L.red[0][g_own * nrb + r_own] = m;
   __syncthreads();
   m = L.red[0][r_own];
   for (int g = 1; g < kFinThreads / group; ++g) m = fmaxf(m, L.red[0][g * nrb + r_own]);
   float l = 0.f;
-  for (int t = t_own; t < tn; t += tstep) {
+  each(0, tn, [&](int t) {
     const float2 v = st(t);
     l += v.y * fast_exp2(v.x - m);
-  }
+  });
   for (int off = 32; off >= nrb; off >>= 1) l += __shfl_xor(l, off);
   if (writes) L.red[1][g_own * nrb + r_own] = l;
   __syncthreads();
@@ -103,8 +118,7 @@ __device__ __forceinline__ void finalize_row(const float* __restrict__ part,
   const int jper = kTsub / nrb;  // key blocks per sub-tile
   for (int t0 = 0; t0 < tn; t0 += tchunk) {
     const int t1 = min(t0 + tchunk, tn);
-    for (int t = t0 + t_own; t < t1; t += tstep)
-      L.f[(t - t0) * nrb + r_own] = fast_exp2(st(t).x - m) * il;
+    each(t0, t1, [&](int t) { L.f[(t - t0) * nrb + r_own] = fast_exp2(st(t).x - m) * il; });
     __syncthreads();
     const int j_lo = t0 * jper, j_hi = min(t1 * jper, ncand);
     auto factor = [&](int r, int t) -> float { return L.f[(t - t0) * nrb + r]; };

@@ -21,6 +21,7 @@
 #include <utility>
 
 #include "common.h"
+#include "dispatch.h"
 #include "score_rows.h"
 #include "select_rows.h"
 
@@ -28,9 +29,9 @@ using namespace xattn;
 
 namespace {
 
-constexpr int TM = 256;             // reduced rows (R) and columns (c) per workgroup tile
+constexpr int TM = kTileMax;        // reduced rows (R) and columns (c) per workgroup tile
 constexpr int TSUB = kTsub;         // column sub-tile owning one (m, l) pair per row
-constexpr int KC = 64;              // reduced-K chunk per pipeline stage (128-byte rows)
+constexpr int KC = kChunk;          // reduced-K chunk per pipeline stage (128-byte rows)
 constexpr int NSTAGE = 2;           // stages: one chunk computed while the next loads
 constexpr int kThreads = 512;       // 8 waves: 2 (columns) x 4 (rows), 128 c x 64 R each
 constexpr int kStage = TM * KC;     // bf16 elements of one operand in one stage
@@ -39,8 +40,6 @@ constexpr int kRowsPer256 = 128 / KC;  // LDS rows per 256-byte bank period
 constexpr int kDmaRows = 512 / KC;  // rows one 1 KB direct-to-LDS instruction fills
 constexpr int kDmaPerOp = 32 / kDmaRows;  // instructions per wave per operand per chunk
 static_assert(NSTAGE * 2 * kStage * 2 <= 160 * 1024, "LDS budget");
-
-__host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 __device__ __forceinline__ void tri_decode(int t, int& rt, int& ct) {
   int r = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
@@ -438,15 +437,6 @@ struct SmallTile {
   static constexpr int kStageElems = kRows * KC;
 };
 
-// Tiles of a head: row tile rt has (rt RT) / 128 + 1 column tiles when causal.
-template <int RT, bool CAUSAL>
-__host__ __device__ inline int small_tiles(int NR) {
-  const int nrt = ceil_div(NR, RT), k = TSUB / RT, nct = ceil_div(NR, TSUB);
-  if (!CAUSAL) return nrt * nct;
-  const int g = (nrt - 1) / k;
-  return k * (g * (g + 1) / 2) + (nrt - g * k) * (g + 1);
-}
-
 // f(integral_constant<int, I>) for every I of the sequence, in order.
 template <int... I, typename F>
 __device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>, F&& f) {
@@ -760,7 +750,7 @@ template <int NRB, bool CAUSAL, int RT>
 hipError_t launch_small(const void* q, const void* k, const XattnShape& s,
                         const SubRowPairing& pr, float scale_log2, float* part, float* stats,
                         hipStream_t st) {
-  const int NR = s.seq / (kBlock / NRB), tiles = small_tiles<RT, CAUSAL>(NR);
+  const int NR = s.seq / (kBlock / NRB), tiles = small_tiles(RT, CAUSAL, NR);
   const int n_work = s.HQ() * tiles;
   hipLaunchKernelGGL((score_partials_small<NRB, CAUSAL, RT>),
                      dim3(ceil_div(n_work, kNumXcd) * kNumXcd), dim3(256), 0, st,
@@ -773,36 +763,16 @@ template <int NRB, bool CAUSAL>
 hipError_t launch_partials(const void* q, const void* k, const XattnShape& s,
                            const SubRowPairing& pr, float* part, float* stats, hipStream_t st) {
   const int S = kBlock / NRB, NR = s.seq / S, NB = s.NB(), NT = ceil_div(NR, TSUB);
-  const int T = ceil_div(NR, TM);
-  const int tiles = CAUSAL ? T * (T + 1) / 2 : T * T;
+  const int tiles = large_tiles(CAUSAL, NR);
   const int n_work = s.batch * s.hkv * tiles * (s.hq / s.hkv);
   const float scale_log2 = kLog2e / (sqrtf((float)kHeadDim) * (float)S);
   // one resident workgroup per CU (128 KB of LDS each), a multiple of 8
   const int wgs = persistent_workgroups();
-  // The tile whose rounds over the chip (one workgroup per CU) cost least: a
-  // round takes a chunk's time (1.1 us per 64-deep chunk of 256 x 256, 0.52 of
-  // 128 x 128, 0.42 of 128 x 64, 0.30 of 128 x 32: a smaller tile moves more
-  // bytes per product but is done sooner) for each of its NCH chunks, and its
-  // start and epilogue (8 / 3.6 / 2.5 / 1.8 us), all measured with every CU
-  // busy. Small tiles win while the 256 x 256 ones leave CUs idle: xattn_score
-  // at 4K tokens, one head, S = 8 (3 such tiles): 29 -> 13 us; two 4736-token
-  // prompts of 8 heads, S = 16 (48): 46 -> 19 us; 8K, 32 heads, S = 16 (96):
-  // 51 -> 46 us. From about 200 on they lose: 8K, 32 heads, S = 8 (320): 66 us
-  // against 70 in 128 x 128 tiles.
-  constexpr int NCH = S * kHeadDim / KC;
-  const int heads = s.batch * s.hq;
-  auto rounds = [&](long long tiles_all) { return (tiles_all + wgs - 1) / wgs; };
-  const long long cost[4] = {
-      rounds(n_work) * (110 * NCH + 800),
-      rounds((long long)heads * small_tiles<128, CAUSAL>(NR)) * (52 * NCH + 360),
-      rounds((long long)heads * small_tiles<64, CAUSAL>(NR)) * (42 * NCH + 250),
-      rounds((long long)heads * small_tiles<32, CAUSAL>(NR)) * (30 * NCH + 180)};
-  int best = 0;
-  for (int i = 1; i < 4; ++i)
-    if (cost[i] < cost[best]) best = i;
-  if (best == 1) return launch_small<NRB, CAUSAL, 128>(q, k, s, pr, scale_log2, part, stats, st);
-  if (best == 2) return launch_small<NRB, CAUSAL, 64>(q, k, s, pr, scale_log2, part, stats, st);
-  if (best == 3) return launch_small<NRB, CAUSAL, 32>(q, k, s, pr, scale_log2, part, stats, st);
+  switch (score_tile_rows(s.HQ(), NR, S, CAUSAL, wgs)) {
+    case 128: return launch_small<NRB, CAUSAL, 128>(q, k, s, pr, scale_log2, part, stats, st);
+    case 64: return launch_small<NRB, CAUSAL, 64>(q, k, s, pr, scale_log2, part, stats, st);
+    case 32: return launch_small<NRB, CAUSAL, 32>(q, k, s, pr, scale_log2, part, stats, st);
+  }
   hipLaunchKernelGGL((score_partials<NRB, CAUSAL>), dim3(wgs), dim3(kThreads), 0, st,
                      (const uint16_t*)q, (const uint16_t*)k, s.hq, s.hkv, s.seq, NR, NB, NT,
                      tiles, n_work, scale_log2, pr, part, (float2*)stats);

@@ -1,7 +1,8 @@
 """Block scores (Algorithm 1) where the kernels change their work split,
 against the fp64 oracle on sampled rows: rows whose sub-tile factors fit one
 LDS stage of the finalisation exactly, exceed it by one sub-tile, and take
-several stages; every tile size of the partial sums at ragged lengths."""
+several stages; every kernel of the partial sums (stride, causal or not, tile
+size) at a ragged length."""
 import numpy as np
 import pytest
 
@@ -9,6 +10,7 @@ import oracle
 import workloads as W
 
 from .helpers import compare_scores, dev_bf16, host_f32
+from .score_tiles import CASES, CUS
 
 pytestmark = pytest.mark.gpu
 
@@ -55,7 +57,7 @@ def test_rows_longer_than_one_factor_stage(S, NB, causal):
 
 
 # reduced lengths below, at and just past 32, 64, 128 and 256 rows at every stride, from one
-# head (128 x 32 tiles) to enough of them for 128 x 64, 128 x 128 and 256 x 256 tiles
+# head to many (each kernel by its name: test_every_kernel)
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("S", [1, 2, 4, 8, 16, 32, 64])
 def test_every_tile_size(S, causal):
@@ -73,3 +75,10 @@ def test_ragged_256_row_tiles(S, NB, hq, causal):
 
 def test_batches_on_small_tiles():
     _check(37, 8, 16, True, seed=990, batch=3)
+
+
+@pytest.mark.parametrize("S,causal,tile,hq,NB", CASES)
+def test_every_kernel(S, causal, tile, hq, NB):
+    if torch.cuda.get_device_properties(0).multi_processor_count // 8 * 8 != CUS:
+        pytest.skip(f"the shapes are for {CUS} compute units")
+    _check(NB, hq, S, causal, seed=1000 + NB)

@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "dispatch.h"
 
 using namespace xattn;
 
@@ -124,7 +125,7 @@ __device__ __forceinline__ void attn_body(
   // head, then query block descending (the workgroups resident at any time read
   // the K/V of one group, 64 MB at 128K tokens, which then stays in the
   // Infinity Cache), or by query block descending, then kv head (groups > 0:
-  // heavy causal rows of every head start first; launch_t has the rule).
+  // heavy causal rows of every head start first; attn_by_block has the rule).
   const int w = blockIdx.x;
   const int G = hq / hkv;
   const int hh = w % G;
@@ -646,34 +647,15 @@ hipError_t launch_t(const void* q, const void* k, const void* v, const XattnShap
                     hipStream_t st) {
   const int n_work = s.HQ() * s.NB();
   const float scale_log2 = kLog2e / sqrtf((float)kHeadDim);
-  // The small kernel while its workgroups (four per query block, one per CU)
-  // fit the chip once, or twice where rows are long: one head of 4K tokens,
-  // 54 % of the blocks (32 query blocks), 45 -> 25 us, all of them 61 -> 30 us;
-  // four heads of 2K (64) 26 -> 17.5 us; one head of 16K, 15 % (128), 51 -> 37
-  // us. Beyond, its four-fold traffic costs more than the idle CUs: eight heads
-  // of 2K (128 query blocks of short rows) 26.8 against 29.9 us, one head of
-  // 32K, 20 % (256), 116 against 125 us. Both modes choose alike, so that
-  // dense and full lists give the same bits.
-  if (n_work <= 64 || (n_work <= 128 && s.NB() >= 48)) {
+  if (attn_small(n_work, s.NB(), compute_units())) {
     hipLaunchKernelGGL((attn_small_kernel<CAUSAL>), dim3((n_work + 7) / 8 * 32), dim3(kSmallThreads), 0,
                        st, dense ? 1 : 0, (const uint16_t*)q, (const uint16_t*)k,
                        (const uint16_t*)v, s.hq, s.hkv, s.seq, s.NB(), n_work, idx, cnt,
                        scale_log2, (uint16_t*)o, lse);
     return hipGetLastError();
   }
-  // By query block where rows differ in length (causal) and all heads' K/V
-  // share the caches: kv head after kv head, the light rows of one head run
-  // beside the heavy rows of the next, and the last head's tail leaves CUs
-  // idle. Measured: dense, 4K, 32/8 heads 179 -> 140 us, 16K, 24 heads 1663 ->
-  // 1395 us, 16K, 32/8 1975 -> 1903 us, 32K, 32/8 (128 MB of K/V) 7416 -> 7222
-  // us; lists, two 4736-token prompts, 8/2 heads, 60 %: 85 -> 77 us, 8K, 32/8,
-  // 40 %: 269 -> 254 us, 16K, 24/8, 25 %: 464 -> 455 us. Lists with more rows
-  // or wider groups live off the cache of one group's K/V instead: 16K, 28/4
-  // (3500 rows) 503 against 527 us, 32K, 32/8 (8192 rows) 1436 against 1484 us.
-  const int G = s.hq / s.hkv;
   const size_t kv_bytes = (size_t)2 * s.batch * s.hkv * s.seq * kHeadDim * 2;
-  const bool by_block =
-      CAUSAL && (dense ? kv_bytes <= ((size_t)128 << 20) : n_work <= (G <= 4 ? 4096 : 1024));
+  const bool by_block = attn_by_block(CAUSAL, dense, kv_bytes, n_work, s.hq / s.hkv);
   hipLaunchKernelGGL((attn_kernel<CAUSAL>), dim3(n_work), dim3(kThreads), 0, st, dense ? 1 : 0,
                      by_block ? s.batch * s.hkv : 0,
                      (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, s.hq, s.hkv,

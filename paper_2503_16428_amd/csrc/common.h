@@ -77,6 +77,9 @@ struct XattnShape {
 struct SubRowPairing {
   int q[64];
 };
+// Compute units of the current device, rounded down to a multiple of the 8
+// XCDs (cached per device).
+int compute_units();
 hipError_t launch_score(const void* q, const void* k, const XattnShape& s, int stride,
                         const int32_t* qsub, float* scores, void* scratch, hipStream_t st);
 // launch_score and launch_select with one threshold in two launches instead

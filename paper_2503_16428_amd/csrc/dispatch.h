@@ -60,4 +60,42 @@ inline int score_tile_rows(int heads, int NR, int stride, bool causal, int wgs) 
   return rows[best];
 }
 
+// ---- attention
+
+// 32-query workgroups (attn_small_kernel), four per query block, one per CU:
+// while they fit the chip once, or twice where rows are long. Measured against
+// the 128-query kernel (us, 256 CUs, 3 to 50 % of the blocks and dense):
+//   once (up to 64 query blocks), never slower in 11 shapes, causal and not:
+//   one head of 4K, 50 %, 43 -> 24, dense 61 -> 30; 8 heads of 768 tokens,
+//   dense, 17.4 -> 12.1; one head of 8K, 15 %, 31.5 -> 19.3, dense 115 -> 55;
+//   twice: 2 heads of 6K, 20 %, 36 -> 23; one head of 16K, 20 %, 67 -> 44,
+//   dense 225 -> 130, bidirectional 81 -> 74 and 247 -> 228. Faster from lists
+//   of 6 % on; at 3 % (4 blocks a row) 23 -> 21 to 21.4 -> 23.0, at 2 blocks a
+//   row 13.4 -> 16.0;
+//   twice with shorter rows they lose where rows are alike: 8 heads of 2K,
+//   bidirectional, dense, 36 -> 40, 16 heads of 1K 22 -> 27;
+//   three times: one head of 20K, bidirectional, dense, 294 -> 370.
+// Dense and listed calls choose alike, so that dense and full lists give the
+// same bits.
+inline bool attn_small(int n_work, int NB, int cus) {
+  return 4ll * n_work <= cus || (2ll * n_work <= cus && NB >= 48);
+}
+
+// Work order of attn_kernel: query block first, then kv head, where rows differ
+// in length (causal) and all heads' K/V share the caches; kv head after kv
+// head, the light rows of one head run beside the heavy rows of the next, and
+// the last head's tail leaves CUs idle. Measured, us: dense, 4K, 32/8 heads 179
+// -> 140, 16K, 24 heads 1663 -> 1395, 32K, 32/8 (128 MB of K/V) 7416 -> 7222;
+// lists, groups of up to 4: 4K, 24/8 (768 rows) 94 -> 70, 8K, 32/8 (2048) 220
+// -> 203, 16K, 32/8 (4000) 586 -> 581, 32K, 12/4 (3000) 505 -> 511, 16/16
+// (4000) 721 -> 692; groups of 5 to 8: 4K, 28/4 (896) 94 -> 80, 8K, 28/4 (1792)
+// 184 -> 176, 64/8 at 4K (2048) 188 -> 175, 16K, 16/2 (2000) 286 -> 286. Lists
+// with more rows live off the cache of one group's K/V instead: 32K, 32/8
+// (8000) 1351 -> 1389, 16K, 64/16 (8000) 1148 -> 1200, and for wide groups 16K,
+// 28/4 (3500) 498 -> 507, 8K, 64/8 (4096) 409 -> 416.
+inline bool attn_by_block(bool causal, bool dense, size_t kv_bytes, int n_work, int group) {
+  if (!causal) return false;
+  return dense ? kv_bytes <= ((size_t)128 << 20) : n_work <= (group <= 4 ? 4096 : 2048);
+}
+
 }  // namespace xattn

@@ -727,25 +727,6 @@ __global__ __launch_bounds__(kFinThreads) void score_finalize_select(
                                cnt + row, stage);
 }
 
-// Compute units of the current device, rounded down to a multiple of the 8
-// XCDs (cached per device).
-int persistent_workgroups() {
-  static std::atomic<int> cached[64];  // static storage: starts at zero
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-  const bool cacheable = dev >= 0 && dev < 64;
-  int n = cacheable ? cached[dev].load(std::memory_order_relaxed) : 0;
-  if (n == 0) {
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < kNumXcd)
-      cus = 256;  // any multiple of 8 is a valid grid; this only sizes it
-    n = cus / kNumXcd * kNumXcd;
-    if (cacheable) cached[dev].store(n, std::memory_order_relaxed);
-  }
-  return n;
-}
-
 template <int NRB, bool CAUSAL, int RT>
 hipError_t launch_small(const void* q, const void* k, const XattnShape& s,
                         const SubRowPairing& pr, float scale_log2, float* part, float* stats,
@@ -767,7 +748,7 @@ hipError_t launch_partials(const void* q, const void* k, const XattnShape& s,
   const int n_work = s.batch * s.hkv * tiles * (s.hq / s.hkv);
   const float scale_log2 = kLog2e / (sqrtf((float)kHeadDim) * (float)S);
   // one resident workgroup per CU (128 KB of LDS each), a multiple of 8
-  const int wgs = persistent_workgroups();
+  const int wgs = compute_units();
   switch (score_tile_rows(s.HQ(), NR, S, CAUSAL, wgs)) {
     case 128: return launch_small<NRB, CAUSAL, 128>(q, k, s, pr, scale_log2, part, stats, st);
     case 64: return launch_small<NRB, CAUSAL, 64>(q, k, s, pr, scale_log2, part, stats, st);
@@ -787,6 +768,23 @@ hipError_t launch_partials_c(const void* q, const void* k, const XattnShape& s,
 }
 
 }  // namespace
+
+int compute_units() {
+  static std::atomic<int> cached[64];  // static storage: starts at zero
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+  const bool cacheable = dev >= 0 && dev < 64;
+  int n = cacheable ? cached[dev].load(std::memory_order_relaxed) : 0;
+  if (n == 0) {
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus < kNumXcd)
+      cus = 256;  // any multiple of 8 is a valid grid; this only sizes it
+    n = cus / kNumXcd * kNumXcd;
+    if (cacheable) cached[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
+}
 
 size_t score_scratch_bytes(const XattnShape& s, int stride) {
   const int NR = s.seq / stride, NB = s.NB(), NT = ceil_div(NR, TSUB);

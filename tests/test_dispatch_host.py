@@ -40,3 +40,24 @@ def test_the_scoring_cases_cover_every_kernel(ask):
     for S, _, tile, _, nb in CASES:
         rows = nb * 128 // S
         assert rows > tile and (rows % tile or 128 // S % tile == 0)
+
+
+def test_attention_on_few_query_blocks(ask):
+    """32-query workgroups fit the chip once, or twice with long rows, whatever its size."""
+    shapes = {(1, 1, 64): 2, (16, 4, 4): 2, (13, 1, 5): 1, (2, 1, 47): 1, (2, 1, 48): 2,
+              (1, 1, 128): 2, (1, 1, 129): 1, (8, 1, 16): 1}
+    got = ask([f"attn {hq} {hkv} {nb} 0 256" for hq, hkv, nb in shapes])
+    assert got == list(shapes.values())
+    # half the compute units, half the query blocks
+    assert ask([f"attn 1 1 {nb} 0 128" for nb in (32, 33, 47, 48, 64, 65)]) == [2, 1, 1, 2, 2, 1]
+    for hq, hkv, nb in shapes:  # dense and listed calls alike
+        a, b = ask([f"attn {hq} {hkv} {nb} {dense} 256" for dense in (0, 1)])
+        assert (a == 2) == (b == 2)
+
+
+def test_attention_order(ask):
+    lists = {(32, 8, 128): 1, (32, 8, 129): 0, (16, 16, 256): 1, (28, 4, 73): 1, (28, 4, 74): 0,
+             (64, 8, 32): 1, (10, 2, 205): 0}
+    assert ask([f"attn {hq} {hkv} {nb} 0 256" for hq, hkv, nb in lists]) == list(lists.values())
+    dense = {(32, 8, 256): 1, (32, 8, 257): 0, (24, 24, 85): 1, (24, 24, 86): 0}
+    assert ask([f"attn {hq} {hkv} {nb} 1 256" for hq, hkv, nb in dense]) == list(dense.values())

@@ -407,11 +407,13 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(
 // parity w / 4, and are merged through LDS at the end. A grid of few
 // 128-query workgroups leaves most CUs idle, and each is a serial chain of
 // half-tiles as long as the load latency (1.3 us with 32 KB in flight); this
-// one has four times as many workgroups of half as many steps, 128 KB in
-// flight per CU. The next K and V (16 KB per wave) are loaded a step ahead
-// into registers, in rows, and pass through wave-private LDS for the operand
-// layouts, so no wave waits for another before the merge. It moves four times
-// the bytes per query of the 128-query kernel.
+// one has four times as many workgroups of a quarter as many steps, of 32 keys
+// a wave instead of 64, and 128 KB in flight per CU. The next K and V (16 KB
+// per wave) are loaded a step ahead into registers, in rows, and pass through
+// wave-private LDS for the operand layouts, so no wave waits for another
+// before the merge. It moves four times the bytes per query of the 128-query
+// kernel. Every wave rounds its probabilities against its own reference, so
+// the outputs differ from that kernel's by such roundings.
 constexpr int kSmallWaves = 8;
 constexpr int kSmallThreads = 64 * kSmallWaves;
 constexpr int kKeysW = 32;      // keys of a block per wave

@@ -423,9 +423,10 @@ __global__ __launch_bounds__(kThreads, 1) void score_partials(
 // CUs idle, and each is a serial chain of chunks as long as the load latency;
 // these tiles are 4 to 16 times as many, and a ring of 4 to 6 LDS stages keeps
 // 80 to 120 KB of loads in flight per CU (a chunk of a 128 x 32 tile takes
-// 0.22 us alone, one of a 256 x 256 tile 1.05 us). Every product is added in
-// the same order as in score_partials; only a row's sum l and the masses of
-// blocks wider than a wave's columns are added in another one.
+// 0.22 us alone, one of a 256 x 256 tile 1.05 us). The sums are those of
+// score_partials in another order: 16 products an MFMA and not 32, and a row's
+// columns over other lanes and waves. So a head's scores may differ in their
+// last bits with the number of heads and blocks that choose the tile.
 template <int RT>
 struct SmallTile {
   static constexpr int kWc = RT >= 128 ? 2 : 4;        // waves along the columns

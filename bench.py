@@ -43,7 +43,8 @@ PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA (2.4 GHz)
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 FLUSH_BYTES = 512 << 20        # written before every timed step
 CSRC = os.path.join(ROOT, "paper_2503_16428_amd", "csrc")
-KERNEL_SOURCES = {"attn": ["attn.hip", "common.h"], "score": ["score.hip", "common.h"]}
+KERNEL_SOURCES = {"attn": ["attn.hip", "dispatch.h", "common.h"],
+                  "score": ["score.hip", "score_rows.h", "dispatch.h", "common.h"]}
 
 
 def parse(argv=None):

@@ -5,6 +5,7 @@ matched by workload, kernel, stride, tau and the hash of the kernel's
 sources."""
 import importlib.util
 import os
+import re
 import shutil
 
 import pytest
@@ -66,14 +67,31 @@ def test_read_traffic_matches_configuration_and_kernel_version(bench, tmp_path):
 
 def test_source_hash_follows_the_kernel_sources(bench, tmp_path):
     src = os.path.join(ROOT, "paper_2503_16428_amd", "csrc")
-    for name in ("attn.hip", "score.hip", "common.h"):
+    for name in set(sum(bench.KERNEL_SOURCES.values(), [])):
         shutil.copy(os.path.join(src, name), tmp_path / name)
     a0, s0 = bench.source_hash("attn", str(tmp_path)), bench.source_hash("score", str(tmp_path))
     assert a0 == bench.source_hash("attn") and s0 == bench.source_hash("score")
-    with open(tmp_path / "attn.hip", "a") as fh:
-        fh.write("\n// edit\n")
-    assert bench.source_hash("attn", str(tmp_path)) != a0
-    assert bench.source_hash("score", str(tmp_path)) == s0
+    for name, attn, score in (("attn.hip", True, False), ("score_rows.h", False, True),
+                              ("dispatch.h", True, True)):
+        with open(tmp_path / name, "a") as fh:
+            fh.write("\n// edit\n")
+        a1, s1 = bench.source_hash("attn", str(tmp_path)), bench.source_hash("score", str(tmp_path))
+        assert (a1 != a0) == attn and (s1 != s0) == score
+        a0, s0 = a1, s1
+
+
+@pytest.mark.parametrize("kernel,source", [("attn", "attn.hip"), ("score", "score.hip")])
+def test_source_hash_covers_the_included_headers(bench, kernel, source):
+    """Every header of the library that the kernel's source includes, but the selection's."""
+    src = os.path.join(ROOT, "paper_2503_16428_amd", "csrc")
+    seen, todo = set(), [source]
+    while todo:
+        name = todo.pop()
+        if name not in seen:
+            seen.add(name)
+            text = open(os.path.join(src, name)).read()
+            todo += [h for h in re.findall(r'#include "([^"]+)"', text) if h != "select_rows.h"]
+    assert set(bench.KERNEL_SOURCES[kernel]) | {"score_rows.h"} == seen | {"score_rows.h"}
 
 
 def test_metric_names_and_host_info(bench):

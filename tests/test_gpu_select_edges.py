@@ -90,3 +90,23 @@ def test_forward_lists_are_the_selection_of_its_scores(hq, NB, tau, causal):
     assert torch.equal(views["scores"], sc) and torch.equal(views["cnt"], cnt)
     kept = torch.arange(NB, device="cuda") < cnt[..., None]
     assert torch.equal(views["idx"][kept], idx[kept])
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("hq,NB,stride", [(1, 9, 1), (2, 33, 1), (1, 129, 1), (1, 64, 2),
+                                          (3, 65, 2), (2, 257, 2), (1, 65, 4)])
+def test_forward_lists_at_small_strides(hq, NB, stride, causal):
+    """The same where the finalisation keeps several loads of a row's stats in flight."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(NB)
+    q, k, v = (torch.randn((n, NB * 128, 128), generator=g, device="cuda").bfloat16() * 2
+               for n in (hq, 1, 1))
+    print(f"forward lists hq={hq} NB={NB} stride={stride} causal={causal}", flush=True)
+    _, _, views = X.xattn_forward(q, k, v, causal=causal, stride=stride, tau=0.9)
+    sc = X.xattn_score(q, k, causal=causal, stride=stride)
+    idx, cnt = X.xattn_select(sc, X.make_dims(q, k, causal), 0.9)
+    torch.cuda.synchronize()
+    assert torch.allclose(sc.sum(-1), torch.ones_like(sc[..., 0]), atol=1e-4)
+    assert torch.equal(views["scores"], sc) and torch.equal(views["cnt"], cnt)
+    kept = torch.arange(NB, device="cuda") < cnt[..., None]
+    assert torch.equal(views["idx"][kept], idx[kept])

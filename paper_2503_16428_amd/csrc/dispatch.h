@@ -70,8 +70,8 @@ inline int score_tile_rows(int heads, int NR, int stride, bool causal, int wgs) 
 //   dense, 17.4 -> 12.1; one head of 8K, 15 %, 31.5 -> 19.3, dense 115 -> 55;
 //   twice: 2 heads of 6K, 20 %, 36 -> 23; one head of 16K, 20 %, 67 -> 44,
 //   dense 225 -> 130, bidirectional 81 -> 74 and 247 -> 228. Faster from lists
-//   of 6 % on; at 3 % (4 blocks a row) 23 -> 21 to 21.4 -> 23.0, at 2 blocks a
-//   row 13.4 -> 16.0;
+//   of 6 % on; at 3 % one head of 16K 24.9 -> 22.5 and, bidirectional, 26.7 ->
+//   28.6, at 2 blocks a row 13.4 -> 16.1;
 //   twice with shorter rows they lose where rows are alike: 8 heads of 2K,
 //   bidirectional, dense, 36 -> 40, 16 heads of 1K 22 -> 27;
 //   three times: one head of 20K, bidirectional, dense, 294 -> 370.
